@@ -294,7 +294,9 @@ int tde_get_status(const void* ws, void* hip_stream);
  * tde_get_counters: waits for the stream, then copies n (<= 20) counters of the
  * algorithmic work of the last solve that used ws:
  *   [0] pole-term evaluations in secular sweeps, [1] (pole, root) pairs in the
- *   Loewner products, [2] (root, pole) pairs in the boundary-row dot products,
+ *   Loewner products, [2] (root, pole) pairs in the boundary-row dot products
+ *   (a wide block of 64 roots counts each pole it takes into its far-field
+ *   moments once),
  *   [3] secular roots, [4] secular sweeps, [5] columns solved by leaves,
  *   [6] plane rotations applied by QL leaves, [7] columns passed through
  *   merges (summed over tree levels, in-wave leaf merges included);

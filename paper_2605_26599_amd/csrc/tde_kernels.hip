@@ -8,6 +8,7 @@
 #include "tde_plan.h"
 
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace tde {
@@ -841,14 +842,14 @@ __device__ __forceinline__ TileWindow tile_window(long long g0, long long g1, co
 // that index is uniform, so the per-pole (per-root) operands are scalar loads
 // shared by the 64 lanes, and the left/right split and the origin exclusion
 // of the secular sums become loop bounds: only the window next to the
-// block's own roots needs per-lane selects.  The waves' partial results meet
+// block's own roots needs per-lane selects.  Poles far from the block enter
+// through moments formed once (below).  The waves' partial results meet
 // in LDS in a fixed order, so every wave holds the same totals bit for bit.
 // The wide blocks are the trailing blocks of the regular root kernels'
 // grids (block-uniform split); the work items (64-root blocks of the wide
 // merges) are listed once per level by k_wide_items.
 // ---------------------------------------------------------------------------
 static_assert(64 * kWideWaves == kWG, "wide blocks share the regular kernels' workgroup size");
-static_assert(2 * 5 * kWideWaves * 64 <= 2 * 2048, "wide reduction buffers fit the regular kernels' LDS staging area");
 
 // Exclusive scan of the number of 64-root blocks of every wide merge of a level.
 __global__ __launch_bounds__(1024) void k_wide_items(const MergeRec* __restrict__ mr, int M, Work w, int wide_min,
@@ -945,15 +946,219 @@ __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b,
     }
 }
 
-// Wide secular roots with NW waves per block.  red: 2 x 5 x NW x 64 doubles
-// of LDS.  The block iterates until all of its 64 roots have converged.
+// ---------------------------------------------------------------------------
+// Far-field expansions for the wide blocks.  The 64 roots (poles) of a block
+// lie in one short interval [c - h, c + h] of the spectrum, and over it the
+// contribution of every pole with |D_j - c| >= kFarRatio h is smooth: with
+// u = h/(D_j - c) and t = (x - c)/h, 1/(D_j - x) = (u/h) sum_k u^k t^k with
+// |u| <= 1/kFarRatio and |t| <= 1, and kFarTerms terms leave less than
+// 2 * 4^-28 = 3e-17 of it.  So a block sums the moments of its far poles once
+// (one pole per thread, two fused operations per moment) and every later
+// sweep visits only the near poles and evaluates a polynomial: the O(K) cost
+// per root and sweep becomes O(K) per block plus the near window (about four
+// block widths).  All differences (D_j - c, (D_o - c) + tau) are taken before
+// scaling, so they carry a relative rounding error only, and on either side
+// the moments' terms sum with at most (1 + 1/4)/(1 - 1/4) times the
+// cancellation-free sum: no more rounding than the direct sum over K poles.
+// A root next to a pole sees that pole among the near ones, as exactly as
+// before.  Fewer than kFarMin far poles are swept directly.
+//
+// kFarRatio and kFarTerms: the far poles cost 2 kFarTerms operations per pole
+// and block, the near ones 13 per pole, root and sweep; ratio 4 with 28 terms
+// balances the two at K of a few ten thousand.
+// Measured (Toeplitz n = 65536, seven wide levels, K up to 32768, against
+// sweeps over all poles, which were FP64-issue-bound at 33% of the peak):
+// secular 9.22 -> 0.78 ms, Loewner 1.75 -> 0.44, rows 1.61 -> 0.61, the solve
+// 13.7 -> 3.13 ms, its largest error unchanged (5e-16 of the spectrum's norm).
+// ---------------------------------------------------------------------------
+constexpr int kFarTerms = 28;
+constexpr int kFarFold = 32;  // kFarTerms padded to the fold's power of two
+constexpr double kFarRatio = 4.0;
+constexpr int kFarMin = 192;
+// LDS of the expansions: NW folded partials and two coefficient sets.
+constexpr int far_lds(int nw) { return (nw + 2) * kFarFold; }
+
+// How many of the ascending D[0..n) are <= x (LE) or < x: a 64-ary search by
+// a full wave (uniform arguments and result).
+template <bool LE>
+__device__ __forceinline__ int wave_count(const double* __restrict__ D, int n, double x) {
+    const int lane = threadIdx.x & 63;
+    auto below = [&](int i) { return LE ? (D[i] <= x) : (D[i] < x); };
+    int lo = 0, hi = n;
+    while (hi - lo > 64) {
+        const long long r = hi - lo;
+        const int q = lo + (int)((r * (lane + 1)) / 65);
+        const int c = __builtin_amdgcn_readfirstlane((int)__popcll(__ballot(below(q))));
+        // the answer lies after the c-th probe and at or before the next one
+        const int nlo = c ? lo + (int)((r * c) / 65) + 1 : lo;
+        const int nhi = (c < 64) ? lo + (int)((r * (c + 1)) / 65) : hi;
+        lo = nlo;
+        hi = nhi;
+    }
+    const int q = lo + lane;
+    return __builtin_amdgcn_readfirstlane(lo + (int)__popcll(__ballot(q < hi && below(q))));
+}
+
+struct FarWindow {
+    double c, h, rh;  // interval [c - h, c + h], rh = 1/h
+    int n0, n1;       // near poles [n0, n1), containing [i0, i1]
+    bool far;         // the others enter through moments
+};
+// Interval [D[i0], D[i1]] (i0 < i1) of a merge's poles.
+__device__ __forceinline__ FarWindow far_window(const double* __restrict__ D, int K, int i0, int i1) {
+    FarWindow f;
+    const double lo = D[i0], hi = D[i1];
+    f.c = 0.5 * (lo + hi);
+    f.h = fmax(hi - f.c, f.c - lo);
+    f.rh = 1.0 / f.h;
+    f.n0 = min(wave_count<true>(D, K, f.c - kFarRatio * f.h), i0);
+    f.n1 = max(wave_count<false>(D, K, f.c + kFarRatio * f.h), i1 + 1);
+    // (an interval so narrow that 1/h or a power of u could leave the range
+    // of normal numbers is swept directly)
+    f.far = K - (f.n1 - f.n0) >= kFarMin && f.h > 1e-100;
+    if (!f.far) {
+        f.n0 = 0;
+        f.n1 = K;
+    }
+    return f;
+}
+
+// Wave totals of kFarFold values per lane: lane l returns the total of value
+// l / 2 (the lanes exchange halves of what they hold, then quarters, ...).
+template <int Half>
+__device__ __forceinline__ void wave_fold_step(double (&m)[kFarFold]) {
+    const bool up = ((threadIdx.x & 63) & (2 * Half)) != 0;
+#pragma unroll
+    for (int i = 0; i < Half; ++i) {
+        const double give = up ? m[i] : m[i + Half];
+        const double keep = up ? m[i + Half] : m[i];
+        m[i] = keep + __shfl_xor(give, 2 * Half, 64);
+    }
+}
+__device__ __forceinline__ double wave_fold(double (&m)[kFarFold]) {
+    static_assert(kFarFold == 32, "five halvings");
+    wave_fold_step<16>(m);
+    wave_fold_step<8>(m);
+    wave_fold_step<4>(m);
+    wave_fold_step<2>(m);
+    wave_fold_step<1>(m);
+    return m[0] + __shfl_xor(m[0], 1, 64);
+}
+
+// Moments over the workgroup: term(j, v, u) gives pole j's first moment v and
+// its ratio u (moment k is the sum of v u^k); j runs over [0, n0) and [n1, K)
+// when both is set, else over [j0, j1) alone.  The kFarTerms totals land in
+// coef (LDS) after the closing barrier.  part: NW x kFarFold doubles of LDS.
+template <int NW, class Term>
+__device__ __forceinline__ void far_moments(int j0, int j1, int j2, int j3, double* part, double* coef, Term term) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double m[kFarFold];
+#pragma unroll
+    for (int k = 0; k < kFarFold; ++k) m[k] = 0.0;
+    const int nl = j1 - j0, nt = nl + (j3 - j2);
+    for (int q = threadIdx.x; q < nt; q += NW * 64) {
+        const int j = (q < nl) ? j0 + q : j2 + (q - nl);
+        double v, u;
+        term(j, &v, &u);
+#pragma unroll
+        for (int k = 0; k < kFarTerms; ++k) {
+            m[k] += v;
+            v *= u;
+        }
+    }
+    const double tot = wave_fold(m);
+    if ((lane & 1) == 0) part[wv * kFarFold + (lane >> 1)] = tot;
+    __syncthreads();
+    if (threadIdx.x < kFarFold) {
+        double x = 0.0;
+        for (int v = 0; v < NW; ++v) x += part[v * kFarFold + threadIdx.x];
+        coef[threadIdx.x] = x;
+    }
+    __syncthreads();
+}
+
+// The polynomial sum_k coef[k] t^k and its derivative by t.
+__device__ __forceinline__ double far_value(const double* coef, double t) {
+    double s = coef[kFarTerms - 1];
+#pragma unroll
+    for (int k = kFarTerms - 2; k >= 0; --k) s = fma(s, t, coef[k]);
+    return s;
+}
+__device__ __forceinline__ double far_value(const double* coef, double t, double* ds) {
+    double s = coef[kFarTerms - 1], d = 0.0;
+#pragma unroll
+    for (int k = kFarTerms - 2; k >= 0; --k) {
+        d = fma(d, t, s);
+        s = fma(s, t, coef[k]);
+    }
+    *ds = d;
+    return s;
+}
+
+// Workgroup total (every thread gets the same bits); red: NW doubles of LDS,
+// free for reuse after the next barrier.
+template <int NW>
+__device__ __forceinline__ double wide_total(double x, double* red) {
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    double t = 0.0;
+    for (int v = 0; v < NW; ++v) t += red[v];
+    __syncthreads();
+    return t;
+}
+
+// The last root of a wide merge by the whole workgroup, the poles over its
+// threads: its bracket reaches beyond the poles by up to rho ||z||^2, which
+// would widen its block's interval.  Returns the sweeps after the first,
+// negative at the cap; every thread holds the same root.
+template <int NW>
+__device__ __forceinline__ int wide_last_root(int K, const double* __restrict__ D, const double* __restrict__ Z,
+                                              const double* __restrict__ W, double rho, int cap, double* red,
+                                              SecRoot* r) {
+    double zz = 0.0;
+    for (int j = threadIdx.x; j < K; j += NW * 64) zz += W[j];
+    zz = wide_total<NW>(zz, red);
+    sec_start_last(K, D, Z, rho, zz, r);
+    const double Do = D[K - 1];
+    for (int it = 1; it <= cap; ++it) {
+        double ps = 0.0, dps = 0.0;
+        _Pragma("unroll 4") for (int j = threadIdx.x; j < K - 1; j += NW * 64) {
+            const double q = rcp_nr((D[j] - Do) - r->tau);
+            const double t = W[j] * q;
+            ps += t;
+            dps = fma(t, q, dps);
+        }
+        ps = wide_total<NW>(ps, red);
+        dps = wide_total<NW>(dps, red);
+        if (sec_update(r, rho, ps, dps, 0.0, 0.0, -ps)) return it;
+    }
+    return -1;
+}
+
+// LDS of the wide steps with NW waves per block (doubles).
+constexpr int wide_secular_lds(int nw) { return 2 * 4 * nw * 64 + far_lds(nw); }
+constexpr int wide_lowner_lds(int nw) { return nw * 64 + far_lds(nw) + nw; }
+constexpr int wide_rows_lds(int nw) { return 3 * nw * 64 + (nw + 3) * kFarFold; }
+static_assert(wide_secular_lds(kWideWaves) <= 2 * kStage && wide_lowner_lds(kWideWaves) <= 2 * kStage &&
+                  wide_rows_lds(kWideWaves) <= 4 * kStageRows,
+              "wide buffers fit the regular kernels' LDS staging area");
+
+// Wide secular roots with NW waves per block.  red: wide_secular_lds(NW)
+// doubles of LDS.  The far poles enter through their moments (left and right
+// ones apart, for the two sides' separate sums); the waves split the near
+// ones, waves 0 and 1 also evaluate the left and the right polynomial.  The
+// block iterates until all of its 64 roots have converged; the merge's last
+// root is then solved by the whole block.
 template <int NW>
 __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int M, const double* __restrict__ e,
                              const unsigned long long* __restrict__ pmax, const Work& w, const int* items,
                              double* red) {
     const int lane = threadIdx.x & 63;
     const int wv = wave_uniform((int)(threadIdx.x >> 6));
-    auto R5 = [&](int buf, int q, int v) -> double& { return red[((buf * 5 + q) * NW + v) * 64 + lane]; };
+    auto R4 = [&](int buf, int q, int v) -> double& { return red[((buf * 4 + q) * NW + v) * 64 + lane]; };
+    double* part = red + 2 * 4 * NW * 64;
+    double* coef = part + NW * kFarFold;  // left, right
     const int total = items[M];
     int buf = 0;
     int bad = 0;
@@ -967,78 +1172,106 @@ __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, 
         const int k0 = __builtin_amdgcn_readfirstlane((item - items[m]) * 64);
         const double* D = w.Da + ks;
         const double* Z = w.Za + ks;
+        const double* Wt = w.Wa + ks;
         cdouble* Dc = as_const(D);
-        cdouble* Wc = as_const(w.Wa + ks);
+        cdouble* Wc = as_const(Wt);
         double sgn;
         const double rho = merge_rho(R, e, pmax, &sgn);
         const int k = min(k0 + lane, K - 1);
         const bool act = (k0 + lane) < K;
         const int kk = min(k, K - 2);
         const int klast = min(k0 + 63, K - 1);
-        const int w0 = k0, w1 = min(min(klast, K - 2) + 2, K);
-        const int a = (int)((long long)K * wv / NW), b = (int)((long long)K * (wv + 1) / NW);
-        // first sweep: bracket midpoint with origin kk (the last root also needs ||z||^2)
-        WideSums s{0.0, 0.0, 0.0, 0.0, 0.0};
-        wide_sweep<true>(Dc, Wc, a, b, w0, w1, D[kk], 0.5 * (D[kk + 1] - D[kk]), kk, kk + 2, s);
-        double tot[5];
-        R5(buf, 0, wv) = s.ps;
-        R5(buf, 1, wv) = s.dps;
-        R5(buf, 2, wv) = s.ph;
-        R5(buf, 3, wv) = s.dph;
-        R5(buf, 4, wv) = s.zz;
-        __syncthreads();
-        for (int q = 0; q < 5; ++q) {
-            double x = 0.0;
-            for (int v = 0; v < NW; ++v) x += R5(buf, q, v);
-            tot[q] = x;
-        }
-        buf ^= 1;
-        SecRoot r;
-        bool done;
-        if (k < K - 1) {
-            done = sec_start_interior(k, D, Z, rho, tot[0], tot[1], tot[2], tot[3], &r);
-        } else {
-            sec_start_last(K, D, Z, rho, tot[4], &r);
-            done = false;
-        }
+        const int kin = min(klast, K - 2);  // the block's last interior root
+        SecRoot r{};
+        bool done = k == K - 1;  // solved apart, below
         int its = 0;
-        for (int it = 1; it <= w.sec_cap; ++it) {
-            if (__all(done)) break;
-            const int L1 = r.orgl ? kk : kk + 1;
-            const int R0 = r.orgl ? kk + 1 : kk + 2;
-            WideSums u{0.0, 0.0, 0.0, 0.0, 0.0};
-            wide_sweep<false>(Dc, Wc, a, b, w0, w1, D[r.o], r.tau, L1, R0, u);
-            R5(buf, 0, wv) = u.ps;
-            R5(buf, 1, wv) = u.dps;
-            R5(buf, 2, wv) = u.ph;
-            R5(buf, 3, wv) = u.dph;
-            __syncthreads();
-            for (int q = 0; q < 4; ++q) {
-                double x = 0.0;
-                for (int v = 0; v < NW; ++v) x += R5(buf, q, v);
-                tot[q] = x;
+        if (k0 <= kin) {  // block-uniform
+            const int w0 = k0, w1 = kin + 2;
+            const FarWindow fw = far_window(D, K, k0, kin + 1);
+            if (fw.far) {
+                auto term = [&](int j, double* v, double* u) {
+                    const double q = rcp_nr(D[j] - fw.c);
+                    *v = Wt[j] * q;
+                    *u = fw.h * q;
+                };
+                far_moments<NW>(0, fw.n0, 0, 0, part, coef, term);
+                far_moments<NW>(fw.n1, K, 0, 0, part, coef + kFarFold, term);
             }
-            buf ^= 1;
-            if (!done && sec_update(&r, rho, tot[0], tot[1], tot[2], tot[3], tot[2] - tot[0])) {
-                done = true;
-                its = it;
+            const int nn = fw.n1 - fw.n0;
+            const int a = fw.n0 + (int)((long long)nn * wv / NW), b = fw.n0 + (int)((long long)nn * (wv + 1) / NW);
+            double tot[4];
+            auto sweep = [&](double Do, double tau, int L1, int R0) {
+                WideSums u{0.0, 0.0, 0.0, 0.0, 0.0};
+                wide_sweep<false>(Dc, Wc, a, b, w0, w1, Do, tau, L1, R0, u);
+                if (fw.far && wv < 2) {
+                    double ds;
+                    const double v = far_value(coef + wv * kFarFold, ((Do - fw.c) + tau) * fw.rh, &ds);
+                    ds *= fw.rh;
+                    if (wv == 0) {
+                        u.ps += v;
+                        u.dps += ds;
+                    } else {
+                        u.ph += v;
+                        u.dph += ds;
+                    }
+                }
+                R4(buf, 0, wv) = u.ps;
+                R4(buf, 1, wv) = u.dps;
+                R4(buf, 2, wv) = u.ph;
+                R4(buf, 3, wv) = u.dph;
+                __syncthreads();
+                for (int q = 0; q < 4; ++q) {
+                    double x = 0.0;
+                    for (int v = 0; v < NW; ++v) x += R4(buf, q, v);
+                    tot[q] = x;
+                }
+                buf ^= 1;
+            };
+            // first sweep: bracket midpoint with origin kk
+            sweep(D[kk], 0.5 * (D[kk + 1] - D[kk]), kk, kk + 2);
+            if (!done) done = sec_start_interior(k, D, Z, rho, tot[0], tot[1], tot[2], tot[3], &r);
+            for (int it = 1; it <= w.sec_cap; ++it) {
+                if (__all(done)) break;  // the same in every wave
+                const int L1 = r.orgl ? kk : kk + 1;
+                const int R0 = r.orgl ? kk + 1 : kk + 2;
+                sweep(D[r.o], r.tau, L1, R0);
+                if (!done && sec_update(&r, rho, tot[0], tot[1], tot[2], tot[3], tot[2] - tot[0])) {
+                    done = true;
+                    its = it;
+                }
+            }
+            if (!done) bad = 1;
+            if (wv == 0 && act && k < K - 1) {
+                const unsigned long long sw = (unsigned long long)((done ? its : w.sec_cap) + 1);
+                sweeps += sw;
+                terms += sw * (unsigned long long)nn;
+                if (lane == 0) terms += (unsigned long long)(K - nn);
+                roots += 1;
             }
         }
-        if (!done) bad = 1;
+        if (klast == K - 1) {  // block-uniform
+            __syncthreads();
+            SecRoot q;
+            const int it = wide_last_root<NW>(K, D, Z, Wt, rho, w.sec_cap, part, &q);
+            if (it < 0) bad = 1;
+            if (k == K - 1) r = q;
+            if (threadIdx.x == 0) {
+                const unsigned long long sw = (unsigned long long)((it < 0 ? w.sec_cap : it) + 1);
+                sweeps += sw;
+                terms += sw * (unsigned long long)K;
+                roots += 1;
+            }
+        }
         if (wv == 0 && act) {
             w.org[ks + k] = r.o;
             w.tau[ks + k] = r.tau;
             const double dor = D[r.o];
             w.dorg[ks + k] = dor;
             w.rootval[ks + k] = dor + r.tau;
-            const unsigned long long sw = (unsigned long long)((done ? its : w.sec_cap) + 1);
-            sweeps += sw;
-            terms += sw * (unsigned long long)K;
-            roots += 1;
         }
         __syncthreads();
     }
-    if (bad && wv == 0 && lane == 0) atomicOr(w.status, ST_SEC_NOCONV);
+    if (bad && wv == 0) atomicOr(w.status, ST_SEC_NOCONV);
     if (wv == 0) {
         count_add(w.counters, CNT_SEC_TERMS, terms);
         count_add(w.counters, CNT_SWEEPS, sweeps);
@@ -1046,19 +1279,29 @@ __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, 
     }
 }
 
-// Wide Loewner step: 64 poles per workgroup, the roots split over the waves
-// (root index wave-uniform: D_org, tau and the neighbouring poles are scalar
-// loads).  Factors are multiplied in chunks of 8 numerators and 8
-// denominators, one division per chunk.  red: NW x 64 doubles.  DORG: take
-// D_org of each root from w.dorg (written by secular_wide in the same
-// forward level) instead of gathering D[org[k]], so the scalar loads of one
+// Wide Loewner step: 64 poles per workgroup, the near roots split over the
+// waves (root index wave-uniform: D_org, tau and the neighbouring poles are
+// scalar loads).  Factors are multiplied in chunks of 8 numerators and 8
+// denominators, one division per chunk.  red: wide_lowner_lds(NW) doubles.
+// DORG: take D_org of each root from w.dorg (written by secular_wide in the
+// same forward level) instead of gathering D[org[k]], so the loads of one
 // factor do not wait on each other.
+// A far factor (lambda - D_i)/(D - D_i), D the pole paired with the root,
+// is (lambda - c)/(D - c) times (1 - v t)/(1 - u t) with v = h/(lambda - c),
+// u = h/(D - c): the first parts multiply into one constant of the block, the
+// logarithms of the second sum to a polynomial in t with coefficients
+// (u^m - v^m)/m.  u - v = h (lambda - D)/((lambda - c)(D - c)) comes from the
+// root's own offset and u^(m+1) - v^(m+1) = u (u^m - v^m) + v^m (u - v), so
+// nothing cancels.
 template <int NW, bool DORG>
 __device__ void lowner_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int M, const double* __restrict__ e,
                             const unsigned long long* __restrict__ pmax, const Work& w, bool with_root,
                             const int* items, double* red) {
     const int lane = threadIdx.x & 63;
     const int wv = wave_uniform((int)(threadIdx.x >> 6));
+    double* part = red + NW * 64;
+    double* coef = part + NW * kFarFold;
+    double* cprod = coef + 2 * kFarFold;
     const int total = items[M];
     unsigned long long pairs = 0;
     for (int item = bid; item < total; item += nbw) {
@@ -1069,15 +1312,84 @@ __device__ void lowner_wide(int bid, int nbw, const MergeRec* __restrict__ mr, i
             const int K = wave_uniform(sp.K);
             const long long ks = wave_uniform(sp.ks);
             const int i0 = __builtin_amdgcn_readfirstlane((item - items[m]) * 64);
-            cdouble* D = as_const(w.Da + ks);
+            const double* Dv = w.Da + ks;
+            cdouble* D = as_const(Dv);
             cint* og = as_const(w.org + ks);
             cdouble* dg = as_const(w.dorg + ks);
             cdouble* ta = as_const(w.tau + ks);
             auto dorg = [&](int k) -> double { return DORG ? dg[k] : D[og[k]]; };
             const int i = min(i0 + lane, K - 1);
-            const double di = w.Da[ks + i];
+            const double di = Dv[i];
             const int ilast = min(i0 + 63, K - 1);
-            const int a = (int)((long long)K * wv / NW), b = (int)((long long)K * (wv + 1) / NW);
+            // near roots [f0, f1): a far root lies, with both of its
+            // bracketing poles, on one side outside the near poles
+            FarWindow fw{};
+            int f0 = 0, f1 = K;
+            if (i0 < ilast) {
+                fw = far_window(Dv, K, i0, ilast);
+                if (fw.far) {
+                    f0 = min(max(fw.n0 - 1, 0), i0);
+                    f1 = max(min(fw.n1, K - 1), ilast + 1);
+                }
+            }
+            double cfar = 1.0;
+            if (fw.far) {
+                const double* og_tau = w.tau + ks;
+                const int* og_v = w.org + ks;
+                const double* dg_v = w.dorg + ks;
+                double pn = 1.0, pd = 1.0, prod = 1.0;
+                int cnt = 0;
+                double mm[kFarFold];
+#pragma unroll
+                for (int q = 0; q < kFarFold; ++q) mm[q] = 0.0;
+                const int nf = f0 + (max(K - 1, f1) - f1);
+                for (int q = threadIdx.x; q < nf; q += NW * 64) {
+                    const bool left = q < f0;
+                    const int k = left ? q : f1 + (q - f0);
+                    const double Dk = left ? Dv[k] : Dv[k + 1];
+                    const double dor = DORG ? dg_v[k] : Dv[og_v[k]];
+                    const double tk = og_tau[k];
+                    const double dl = (dor - fw.c) + tk, dd = Dk - fw.c;
+                    pn *= dl;
+                    pd *= dd;
+                    if (++cnt == 8) {
+                        prod *= pn / pd;
+                        pn = 1.0;
+                        pd = 1.0;
+                        cnt = 0;
+                    }
+                    const double rl = rcp_nr(dl), rd = rcp_nr(dd);
+                    const double u = fw.h * rd, v = fw.h * rl;
+                    double vm = u * (((dor - Dk) + tk) * rl);  // v^m (u - v)
+                    double em = vm;                            // u^m - v^m
+                    mm[0] += em;
+#pragma unroll
+                    for (int x = 1; x < kFarTerms; ++x) {
+                        vm *= v;
+                        em = fma(u, em, vm);
+                        mm[x] += em;
+                    }
+                }
+                prod *= pn / pd;
+                for (int o = 32; o > 0; o >>= 1) prod *= __shfl_xor(prod, o, 64);
+                if (lane == 0) cprod[wv] = prod;
+                const double tot = wave_fold(mm);
+                if ((lane & 1) == 0) part[wv * kFarFold + (lane >> 1)] = tot;
+                __syncthreads();
+                if (threadIdx.x < kFarFold) {
+                    double x = 0.0;
+                    for (int v = 0; v < NW; ++v) x += part[v * kFarFold + threadIdx.x];
+                    coef[threadIdx.x] = x / (double)(threadIdx.x + 1);
+                }
+                __syncthreads();
+                if (wv == 0) {
+                    for (int v = 0; v < NW; ++v) cfar *= cprod[v];
+                    const double t = (di - fw.c) * fw.rh;
+                    cfar *= exp(t * far_value(coef, t));
+                }
+            }
+            const int nn = f1 - f0;
+            const int a = f0 + (int)((long long)nn * wv / NW), b = f0 + (int)((long long)nn * (wv + 1) / NW);
             double prod = 1.0, pn = 1.0, pd = 1.0;
             int c = 0;
             auto factor = [&](double num, double den) {
@@ -1103,18 +1415,23 @@ __device__ void lowner_wide(int bid, int nbw, const MergeRec* __restrict__ mr, i
             // ilast < k < K-1: every lane has i <= k
             const int e3 = min(b, K - 1);
             for (int k = max(a, ilast + 1); k < e3; ++k) factor((dorg(k) - di) + ta[k], D[k + 1] - di);
-            if (b == K && ilast + 1 <= K - 1) factor((dorg(K - 1) - di) + ta[K - 1], 1.0);
+            // the last root stands alone (no pole above it): the last wave's,
+            // unless the window above held it
+            if (wv == NW - 1 && ilast + 1 <= K - 1) factor((dorg(K - 1) - di) + ta[K - 1], 1.0);
             prod *= pn / pd;
             red[wv * 64 + lane] = prod;
             __syncthreads();
             if (wv == 0 && i0 + lane < K) {
-                double p = 1.0;
+                double p = cfar;
                 for (int v = 0; v < NW; ++v) p *= red[v * 64 + lane];
                 double sgn;
                 const double rho = merge_rho(R, e, pmax, &sgn);
                 const double zi = sqrt(fmax(p / rho, 0.0));
                 w.zhat[ks + i] = (w.Za[ks + i] < 0.0) ? -zi : zi;
-                if (!(R.flags & MF_ROOT) || w.rows_out) pairs += (unsigned long long)K;
+                if (!(R.flags & MF_ROOT) || w.rows_out) {
+                    pairs += (unsigned long long)nn;
+                    if (lane == 0) pairs += (unsigned long long)(K - nn);
+                }
             }
         }
         __syncthreads();
@@ -1122,15 +1439,19 @@ __device__ void lowner_wide(int bid, int nbw, const MergeRec* __restrict__ mr, i
     if (wv == 0) count_add(w.counters, CNT_LOW_PAIRS, pairs);
 }
 
-// Wide boundary-row step (non-top merges): 64 roots per workgroup, the poles
-// split over the waves, pole index wave-uniform (scalar loads of D_i, zhat_i
-// and both row entries); no pole is excluded, so there is no window.
-// red: 3 x NW x 64 doubles.
+// Wide boundary-row step (non-top merges): 64 roots per workgroup, the near
+// poles split over the waves, pole index wave-uniform (scalar loads of D_i,
+// zhat_i and both row entries); no pole is excluded, so there is no window.
+// The far poles enter through three sets of moments (the norm's with
+// 1/(D - x)^2 = (u/h)^2 sum_k (k + 1) u^k t^k).  The merge's last root goes
+// over all poles with the whole block.  red: wide_rows_lds(NW) doubles.
 template <int NW>
 __device__ void rows_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int M, const Work& w, const int* items,
                           double* red) {
     const int lane = threadIdx.x & 63;
     const int wv = wave_uniform((int)(threadIdx.x >> 6));
+    double* part = red + 3 * NW * 64;
+    double* coef = part + NW * kFarFold;
     const int total = items[M];
     unsigned long long pairs = 0;
     for (int item = bid; item < total; item += nbw) {
@@ -1141,13 +1462,40 @@ __device__ void rows_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int
             const int K = wave_uniform(sp.K);
             const long long ks = wave_uniform(sp.ks);
             const int k0 = __builtin_amdgcn_readfirstlane((item - items[m]) * 64);
-            cdouble* D = as_const(w.Da + ks);
-            cdouble* H = as_const(w.zhat + ks);
-            cdouble* RL = as_const(w.RLa + ks);
-            cdouble* RH = as_const(w.RHa + ks);
+            const double* Dv = w.Da + ks;
+            const double* Hv = w.zhat + ks;
+            const double* Lv = w.RLa + ks;
+            const double* Rv = w.RHa + ks;
+            cdouble* D = as_const(Dv);
+            cdouble* H = as_const(Hv);
+            cdouble* RL = as_const(Lv);
+            cdouble* RH = as_const(Rv);
             const int k = min(k0 + lane, K - 1);
-            const double Do = w.Da[ks + w.org[ks + k]], tau = w.tau[ks + k];
-            const int a = (int)((long long)K * wv / NW), b = (int)((long long)K * (wv + 1) / NW);
+            const int klast = min(k0 + 63, K - 1);
+            const int kin = min(klast, K - 2);
+            const double Do = Dv[w.org[ks + k]], tau = w.tau[ks + k];
+            FarWindow fw{};
+            fw.n1 = K;
+            if (k0 <= kin) fw = far_window(Dv, K, k0, kin + 1);
+            if (fw.far) {
+                auto far = [&](int set, auto weight, bool square) {
+                    far_moments<NW>(0, fw.n0, fw.n1, K, part, coef + set * kFarFold,
+                                    [&](int j, double* v, double* u) {
+                                        const double q = rcp_nr(Dv[j] - fw.c);
+                                        const double y = Hv[j] * q;
+                                        *v = square ? y * y : weight(j) * y;
+                                        *u = fw.h * q;
+                                    });
+                };
+                far(0, [&](int) { return 0.0; }, true);
+                far(1, [&](int j) { return Lv[j]; }, false);
+                far(2, [&](int j) { return Rv[j]; }, false);
+                // (k + 1) times the norm's moments, as its polynomial needs them
+                if (threadIdx.x < kFarTerms) coef[threadIdx.x] *= (double)(threadIdx.x + 1);
+                __syncthreads();
+            }
+            const int nn = fw.n1 - fw.n0;
+            const int a = fw.n0 + (int)((long long)nn * wv / NW), b = fw.n0 + (int)((long long)nn * (wv + 1) / NW);
             double ss = 0.0, bl = 0.0, bh = 0.0;
             _Pragma("unroll 4") for (int i = a; i < b; ++i) {
                 const double y = H[i] * rcp_nr((D[i] - Do) - tau);
@@ -1155,21 +1503,47 @@ __device__ void rows_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int
                 bl = fma(RL[i], y, bl);
                 bh = fma(RH[i], y, bh);
             }
+            if (fw.far && wv < 3) {
+                const double v = far_value(coef + wv * kFarFold, ((Do - fw.c) + tau) * fw.rh);
+                if (wv == 0) ss += v;
+                else if (wv == 1) bl += v;
+                else bh += v;
+            }
             red[(0 * NW + wv) * 64 + lane] = ss;
             red[(1 * NW + wv) * 64 + lane] = bl;
             red[(2 * NW + wv) * 64 + lane] = bh;
             __syncthreads();
-            if (wv == 0 && k0 + lane < K) {
-                double t0 = 0.0, t1 = 0.0, t2 = 0.0;
-                for (int v = 0; v < NW; ++v) {
-                    t0 += red[(0 * NW + v) * 64 + lane];
-                    t1 += red[(1 * NW + v) * 64 + lane];
-                    t2 += red[(2 * NW + v) * 64 + lane];
+            double t0 = 0.0, t1 = 0.0, t2 = 0.0;
+            for (int v = 0; v < NW; ++v) {
+                t0 += red[(0 * NW + v) * 64 + lane];
+                t1 += red[(1 * NW + v) * 64 + lane];
+                t2 += red[(2 * NW + v) * 64 + lane];
+            }
+            if (fw.far && klast == K - 1) {  // block-uniform
+                __syncthreads();
+                const double Dl = Dv[w.org[ks + K - 1]], tl = w.tau[ks + K - 1];
+                double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+                for (int i = threadIdx.x; i < K; i += NW * 64) {
+                    const double y = Hv[i] * rcp_nr((Dv[i] - Dl) - tl);
+                    s0 = fma(y, y, s0);
+                    s1 = fma(Lv[i], y, s1);
+                    s2 = fma(Rv[i], y, s2);
                 }
+                s0 = wide_total<NW>(s0, part);
+                s1 = wide_total<NW>(s1, part);
+                s2 = wide_total<NW>(s2, part);
+                if (k == K - 1) {
+                    t0 = s0;
+                    t1 = s1;
+                    t2 = s2;
+                }
+            }
+            if (wv == 0 && k0 + lane < K) {
                 const double inv = 1.0 / sqrt(t0);
                 w.PBL[ks + k] = t1 * inv;
                 w.PBH[ks + k] = t2 * inv;
-                pairs += (unsigned long long)K;
+                pairs += (unsigned long long)((fw.far && k < K - 1) ? nn : K);
+                if (fw.far && lane == 0) pairs += (unsigned long long)(K - nn);
             }
         }
         __syncthreads();
@@ -1202,7 +1576,7 @@ __device__ void small_merge_fold(int m, const MergeRec* __restrict__ mr, const d
                                  const unsigned long long* __restrict__ pmax, const Work& w, int gmax, int fuse_max,
                                  double* stage, double* out, int amode);
 
-template <int G>
+template <int G, bool Wide>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k_secular(
     const MergeRec* __restrict__ mr, int M, long long N, const double* __restrict__ e,
     const unsigned long long* __restrict__ pmax, Work w, int wide_min, int fuse_max, int nbn, int refill, int nsm,
@@ -1219,7 +1593,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
         small_merge_fold<kWG>((int)blockIdx.x - nbt, mr, e, pmax, w, gmax, fuse_max, smem, out, amode);
         return;
     }
-    if ((int)blockIdx.x >= nbn) {
+    if (Wide && (int)blockIdx.x >= nbn) {
         const int* items = w.witems;
         secular_wide<kWideWaves>((int)blockIdx.x - nbn, nbt - nbn, mr, M, e, pmax, w, items, smem);
         return;
@@ -1396,7 +1770,7 @@ __global__ __launch_bounds__(NW * 64) void k_secular_wide(const MergeRec* __rest
                                                           const unsigned long long* __restrict__ pmax, Work w,
                                                           int wide_min, int fuse_max, int own_items) {
     if (input_nonfinite(w)) return;
-    __shared__ double red[2 * 5 * NW * 64];
+    __shared__ double red[wide_secular_lds(NW)];
     __shared__ int sitems[kWideOwnItems + 1];
     __shared__ int wsum[16];
     __shared__ int carry;
@@ -1433,13 +1807,13 @@ __global__ __launch_bounds__(NW * 64) void k_lowner_wide(const MergeRec* __restr
                                                          const double* __restrict__ e,
                                                          const unsigned long long* __restrict__ pmax, Work w) {
     if (input_nonfinite(w)) return;
-    __shared__ double red[NW * 64];
+    __shared__ double red[wide_lowner_lds(NW)];
     lowner_wide<NW, true>((int)blockIdx.x, (int)gridDim.x, mr, M, e, pmax, w, false, w.witems, red);
 }
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void k_rows_wide(const MergeRec* __restrict__ mr, int M, Work w) {
     if (input_nonfinite(w)) return;
-    __shared__ double red[3 * NW * 64];
+    __shared__ double red[wide_rows_lds(NW)];
     rows_wide<NW>((int)blockIdx.x, (int)gridDim.x, mr, M, w, w.witems, red);
 }
 
@@ -2137,7 +2511,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (threadIdx.x == 0) count_add1(w.counters, CNT_MERGE_COLS, (unsigned long long)s);
 }
 
-template <int G, bool WithRoot>
+template <int G, bool WithRoot, bool Wide>
 __global__ __launch_bounds__(kWG) void k_lowner(const MergeRec* __restrict__ mr, int M, long long N,
                                                 const double* __restrict__ e,
                                                 const unsigned long long* __restrict__ pmax, Work w, int wide_min,
@@ -2168,7 +2542,7 @@ __global__ __launch_bounds__(kWG) void k_lowner(const MergeRec* __restrict__ mr,
         }
         return;
     }
-    if ((int)blockIdx.x >= nbn) {
+    if (Wide && (int)blockIdx.x >= nbn) {
         const int* items = w.witems;
         lowner_wide<kWideWaves, false>((int)blockIdx.x - nbn, nbl - nbn, mr, M, e, pmax, w, WithRoot, items, smem);
         return;
@@ -2213,7 +2587,7 @@ __global__ __launch_bounds__(kWG) void k_lowner(const MergeRec* __restrict__ mr,
 // amode 1 or 2 (no wide blocks then): each root is also placed at its parent
 // position by the lane that stored its rows (body_assemble part 1; 2: 8-way
 // searches), to out for a problem's top merge.
-template <int G>
+template <int G, bool Wide>
 __global__ __launch_bounds__(kWG) void k_rows(const MergeRec* __restrict__ mr, int M, long long N, Work w,
                                               int wide_min, int fuse_max, int nbn,
                                               const unsigned long long* __restrict__ pmax, double* __restrict__ out,
@@ -2222,7 +2596,7 @@ __global__ __launch_bounds__(kWG) void k_rows(const MergeRec* __restrict__ mr, i
     __shared__ double smem[4 * kStageRows];
     __shared__ long long s_r0;
     __shared__ int s_staged;
-    if ((int)blockIdx.x >= nbn) {
+    if (Wide && (int)blockIdx.x >= nbn) {
         const int* items = w.witems;
         rows_wide<kWideWaves>((int)blockIdx.x - nbn, (int)gridDim.x - nbn, mr, M, w, items, smem);
         return;
@@ -2786,16 +3160,15 @@ static void launch_level_block(int smax, const MergeRec* mr, int M, const double
 // no_rows: every merge of the level is a problem's top merge and no rows
 // are requested, so the Loewner and row steps would find nothing to do and
 // are not launched.
-template <int G>
+template <int G, bool Wide>
 static bool launch_roots_g(int smax, int wmin, long long N, const MergeRec* mr, const int* blkm, int M,
                            const double* e, const Work& w, double* out, int gmax, int wblocks, int fuse_few,
                            bool no_rows, void* stream) {
     const unsigned long long* pm = (const unsigned long long*)w.pmax;
     const int fuse_max = level_fuse_max(M, fuse_few);
-    const bool wide = smax >= wmin;
-    const int wide_min = wide ? wmin : 0x7fffffff;
+    const int wide_min = Wide ? wmin : 0x7fffffff;
     int nbn, nbw;
-    root_grid(N, G, wide, &nbn, &nbw, wblocks);
+    root_grid(N, G, Wide, &nbn, &nbw, wblocks);
     // every merge too large for k_small_merge is wide: no regular tiles
     if (wide_min <= fuse_max + 1) nbn = 0;
     // Levels whose roots all come from the fused workgroups and the regular
@@ -2814,7 +3187,7 @@ static bool launch_roots_g(int smax, int wmin, long long N, const MergeRec* mr, 
     // one k_wide_items launch serves the three root kernels of the level (on
     // wide-only levels of few merges the secular kernel builds the table)
     const int own_items = (nbn == 0 && M <= kWideOwnItems) ? 1 : 0;
-    if (wide && !own_items) TDE_LAUNCH_K(KIND_DEFLATE, k_wide_items, 1, 1024, stream, mr, M, w, wide_min, fuse_max);
+    if (Wide && !own_items) TDE_LAUNCH_K(KIND_DEFLATE, k_wide_items, 1, 1024, stream, mr, M, w, wide_min, fuse_max);
     long long rf = (N * G) / kRefillLanes;  // roots per group: keep about kRefillLanes lanes busy
     rf = rf < 1 ? 1 : (rf > kRefillMax ? kRefillMax : rf);
     const int nbs = (int)((nbn + rf - 1) / rf);
@@ -2827,13 +3200,13 @@ static bool launch_roots_g(int smax, int wmin, long long N, const MergeRec* mr, 
         TDE_LAUNCH_K(KIND_ROWS, k_rows_wide<kWideWavesOnly>, (unsigned)nbw, bw, stream, mr, M, w);
         return false;
     }
-    TDE_LAUNCH_K(KIND_SECULAR, k_secular<G>, (unsigned)(nbs + nbw + nsm), kWG, stream, mr, M, N, e, pm, w, wide_min,
+    TDE_LAUNCH_K(KIND_SECULAR, (k_secular<G, Wide>), (unsigned)(nbs + nbw + nsm), kWG, stream, mr, M, N, e, pm, w, wide_min,
                  fuse_max, nbs, (int)rf, nsm, gmax, out, amode);
     if (no_rows) return false;
     const unsigned nba = placed ? nblk(N, kWG) : 0u;
-    TDE_LAUNCH_K(KIND_LOWNER, (k_lowner<G, false>), grid + nba, kWG, stream, mr, M, N, e, pm, w, wide_min, fuse_max,
+    TDE_LAUNCH_K(KIND_LOWNER, (k_lowner<G, false, Wide>), grid + nba, kWG, stream, mr, M, N, e, pm, w, wide_min, fuse_max,
                  nbn, blkm, Grad{}, (int)nba, N <= kWideSearchCols ? 1 : 0, out);
-    TDE_LAUNCH_K(KIND_ROWS, k_rows<G>, grid, kWG, stream, mr, M, N, w, wide_min, fuse_max, nbn, pm, out, amode);
+    TDE_LAUNCH_K(KIND_ROWS, (k_rows<G, Wide>), grid, kWG, stream, mr, M, N, w, wide_min, fuse_max, nbn, pm, out, amode);
     return placed;
 }
 
@@ -2842,13 +3215,22 @@ static bool launch_roots_g(int smax, int wmin, long long N, const MergeRec* mr, 
 static bool launch_roots(int smax, int cols, int wmin, long long N, const MergeRec* mr, const int* blkm, int M,
                          const double* e, const Work& w, double* out, int gmax, int wblocks, int fuse_few,
                          bool no_rows, void* stream) {
+    // (the kernels without wide blocks are instances of their own: a third of
+    // the code, so a level's first workgroups wait less for instructions)
+    const bool wide = smax >= wmin;
+    auto go = [&](auto g) {
+        constexpr int G = decltype(g)::value;
+        return wide ? launch_roots_g<G, true>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows,
+                                              stream)
+                    : launch_roots_g<G, false>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows,
+                                               stream);
+    };
     switch (lanes_per_root(smax, cols)) {
-        case 1: return launch_roots_g<1>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows, stream);
-        case 2: return launch_roots_g<2>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows, stream);
-        case 4: return launch_roots_g<4>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows, stream);
-        case 8: return launch_roots_g<8>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows, stream);
-        default:
-            return launch_roots_g<16>(smax, wmin, N, mr, blkm, M, e, w, out, gmax, wblocks, fuse_few, no_rows, stream);
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        case 8: return go(std::integral_constant<int, 8>{});
+        default: return go(std::integral_constant<int, 16>{});
     }
 }
 
@@ -3006,8 +3388,13 @@ static void launch_bwd_roots_g(int smax, int wmin, long long N, const MergeRec* 
     const unsigned long long* pm = (const unsigned long long*)w.pmax;
     const unsigned nbu = nblk(N, kWG);
     if (wide) TDE_LAUNCH_K(KIND_BACKWARD, k_wide_items, 1, 1024, stream, mr, M, w, wide_min, 0);
-    TDE_LAUNCH_K(KIND_BACKWARD, (k_lowner<G, true>), (unsigned)(nbn + nbw) + nbu, kWG, stream, mr, M, N, e, pm, w,
-                 wide_min, 0, nbn, blkm, gr, (int)nbu, N <= kWideSearchCols ? 1 : 0, (double*)nullptr);
+    const int ws = N <= kWideSearchCols ? 1 : 0;
+    if (wide)
+        TDE_LAUNCH_K(KIND_BACKWARD, (k_lowner<G, true, true>), (unsigned)(nbn + nbw) + nbu, kWG, stream, mr, M, N, e,
+                     pm, w, wide_min, 0, nbn, blkm, gr, (int)nbu, ws, (double*)nullptr);
+    else
+        TDE_LAUNCH_K(KIND_BACKWARD, (k_lowner<G, true, false>), (unsigned)nbn + nbu, kWG, stream, mr, M, N, e, pm, w,
+                     wide_min, 0, nbn, blkm, gr, (int)nbu, ws, (double*)nullptr);
     TDE_LAUNCH_K(KIND_BACKWARD, k_bwd_roots<G>, (unsigned)nbn, kWG, stream, mr, N, w, gr, cs);
     TDE_LAUNCH_K(KIND_BACKWARD, k_bwd_poles<G>, (unsigned)nbn, kWG, stream, mr, N, w, gr, cs);
 }
