@@ -210,9 +210,9 @@ int tde_eigvals_selrows(const double* d, const double* e, int64_t n, const int64
  *   d_out  [n], e_out [n-1]  device, may be NULL: the diagonal and subdiagonal of T
  *   ws     ws_bytes >= tde_dense_workspace_bytes(n, opts) (device): the
  *                   solver's workspace (first, so tde_get_status(ws) reads its
- *                   status), then 64 n + 3 n + 32 doubles of reduction scratch
- * Asynchronous on the stream; the reduction's kernels are enqueued one by
- * one (three per column, one per panel).  Returns TDE_OK or a negative code.
+ *                   status), then about 133 n doubles of reduction scratch
+ * Asynchronous on the stream; the reduction's kernels (two per column, two
+ * per panel) are replayed as a graph like a solve's.  Returns TDE_OK or a negative code.
  * tde_dense_workspace_bytes returns 0 on a bad argument. */
 size_t tde_dense_workspace_bytes(int64_t n, const tde_opts* opts);
 int tde_dense_eigvals(double* A, int64_t n, int64_t lda, double* lambda, double* d_out, double* e_out, void* ws,

@@ -121,3 +121,37 @@ def test_dense_leading_dimension_and_overwrite(tde):
     lam_ow = tde.dense_eigvals(B, overwrite=True).cpu().numpy()
     assert np.array_equal(lam_ow, tde.dense_eigvals(_t(A)).cpu().numpy())
     assert tde.dense_eigvals(torch.zeros((0, 0), dtype=torch.float64, device="cuda:0")).numel() == 0
+
+
+@pytest.mark.parametrize("n", [63, 66, 127, 128, 129, 130, 193, 257, 321])
+def test_dense_tile_edges(tde, n):
+    """Sizes around the 64-row tiles and blocks of the reduction's kernels."""
+    A, _ = _sym(n, 900 + n, "random")
+    _step(f"dense tile edge n={n}")
+    lam, d, e = (x.cpu().numpy() for x in tde.dense_eigvals(_t(A), return_tridiagonal=True))
+    ref = oracle.dense_eigvals(A)
+    tol = GATE * _norm1(A)
+    assert np.abs(lam - ref).max() <= tol
+    # an orthogonal reduction keeps the Frobenius norm
+    fro = float(np.sum(A * A))
+    assert abs((d @ d + 2.0 * e @ e) - fro) <= 1e-12 * fro
+
+
+@pytest.mark.parametrize("n", [4097, 4200])
+def test_dense_large_tiles(tde, n):
+    """Above 4096 rows a tile has several subtiles; two reflections around a
+    known spectrum fix every eigenvalue."""
+    g = np.random.default_rng(n)
+    lam = np.sort(g.uniform(-1.0, 1.0, n))
+    A = np.diag(lam)
+    for _ in range(2):
+        u = g.standard_normal(n)
+        u /= np.linalg.norm(u)
+        w = A @ u
+        A -= 2.0 * np.outer(u, w - (u @ w) * u) + 2.0 * np.outer(w - (u @ w) * u, u)
+    A = 0.5 * (A + A.T)
+    # H A H = A - 2 u w^T - 2 w u^T + 4 (u.w) u u^T, as applied above
+    _step(f"dense large tiles n={n}")
+    out = tde.dense_eigvals(_t(A)).cpu().numpy()
+    assert np.abs(out - lam).max() <= GATE * _norm1(A)
+    assert np.array_equal(out, tde.dense_eigvals(_t(A)).cpu().numpy()), "repeat differs"
