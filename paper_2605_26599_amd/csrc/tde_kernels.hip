@@ -1503,11 +1503,16 @@ __device__ void rows_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int
                 bl = fma(RL[i], y, bl);
                 bh = fma(RH[i], y, bh);
             }
-            if (fw.far && wv < 3) {
-                const double v = far_value(coef + wv * kFarFold, ((Do - fw.c) + tau) * fw.rh);
-                if (wv == 0) ss += v;
-                else if (wv == 1) bl += v;
-                else bh += v;
+            if (fw.far && wv < 2) {
+                // (both row channels in the same wave: a requested row has to
+                // give the same bits in either)
+                const double t = ((Do - fw.c) + tau) * fw.rh;
+                if (wv == 0) {
+                    ss += far_value(coef, t);
+                } else {
+                    bl += far_value(coef + kFarFold, t);
+                    bh += far_value(coef + 2 * kFarFold, t);
+                }
             }
             red[(0 * NW + wv) * 64 + lane] = ss;
             red[(1 * NW + wv) * 64 + lane] = bl;
