@@ -40,6 +40,17 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
+// Wave total of a small per-lane count, in every lane (sums within rows of 16
+// by DPP lane moves, then the four rows).
+__device__ __forceinline__ unsigned wave_sum_u32(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 0) + (unsigned)__builtin_amdgcn_readlane((int)v, 16) +
+           (unsigned)__builtin_amdgcn_readlane((int)v, 32) + (unsigned)__builtin_amdgcn_readlane((int)v, 48);
+}
+
 // Adds a per-lane count to work counter `which` with one atomic per wave,
 // into the slot of this wave.
 __device__ __forceinline__ unsigned long long* count_slot(unsigned long long* c, int which) {
@@ -266,7 +277,7 @@ __device__ __forceinline__ void wave_arrays(WaveLds<Nodes>& sh, Work& wl) {
 
 // Work done by the in-wave levels of one wave (for the counters).
 struct WaveCount {
-    unsigned long long terms = 0, sweeps = 0, roots = 0, lpairs = 0, rpairs = 0, mcols = 0;
+    unsigned terms = 0, sweeps = 0, roots = 0, pairs = 0, mcols = 0;  // (a lane's share, far below 2^32)
     int bad = 0;
 };
 
@@ -299,7 +310,7 @@ __device__ __forceinline__ void wave_level(const MergeRec* smr, int M, int N, co
                                            WaveCount& c) {
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (1ULL << lane) - 1ULL;
-    c.mcols += (lane == 0) ? (unsigned long long)N : 0ULL;
+    c.mcols += (lane == 0) ? (unsigned)N : 0u;
     // merged order, z~, negligible-z flags (lane = child column; its flag
     // lands with it at the merged position)
     if (lane < N) {
@@ -368,8 +379,8 @@ __device__ __forceinline__ void wave_level(const MergeRec* smr, int M, int N, co
         Km = sp.K;
         const int it = body_secular<RedSerial>(lane, m, smr, e, pmax, wl, 0, 1, wl.Da, wl.Wa, 0);
         if (it < 0) c.bad = 1;
-        const unsigned long long sw = (Km > 1) ? (unsigned long long)((it < 0 ? wl.sec_cap : it) + 1) : 0ULL;
-        c.terms += sw * (unsigned long long)Km;
+        const unsigned sw = (Km > 1) ? (unsigned)((it < 0 ? wl.sec_cap : it) + 1) : 0u;
+        c.terms += sw * (unsigned)Km;
         c.roots += 1;
         if (corg) {
             const long long gp = pk0 + smr[m].pk + (lane - sp.ks);
@@ -381,10 +392,7 @@ __device__ __forceinline__ void wave_level(const MergeRec* smr, int M, int N, co
     if (lane < K) body_lowner<RedSerial>(lane, m, smr, e, pmax, wl, 0, 1, wl.Da, wl.org, wl.tau, 0);
     __syncthreads();
     if (lane < K) body_rows<RedSerial>(lane, m, smr, wl, 0, 1, wl.Da, wl.zhat, wl.RLa, wl.RHa, 0);
-    if (rowsm) {
-        c.lpairs += (unsigned long long)Km;
-        c.rpairs += (unsigned long long)Km;
-    }
+    if (rowsm) c.pairs += (unsigned)Km;
     __syncthreads();
     // parent spectra and rows (in place), or the problem's outputs
     if (lane < N) {
@@ -476,11 +484,14 @@ __global__ __launch_bounds__(64) void k_leaf_dc(const LeafRec* __restrict__ leav
         wave_level<0>(sh.smr, M, N, eL, pmax, wl, wt, top, outL, nullptr, nullptr, 0, c);
     }
     if (c.bad) atomicOr(w.status, ST_SEC_NOCONV);
-    count_add(w.counters, CNT_DC_TERMS, c.terms);
-    count_add(w.counters, CNT_DC_ROOTS, c.roots);
-    count_add(w.counters, CNT_DC_LOW_PAIRS, c.lpairs);
-    count_add(w.counters, CNT_DC_ROW_PAIRS, c.rpairs);
-    count_add(w.counters, CNT_MERGE_COLS, c.mcols);
+    const unsigned terms = wave_sum_u32(c.terms), roots = wave_sum_u32(c.roots), pairs = wave_sum_u32(c.pairs);
+    if (lane == 0) {
+        count_add1(w.counters, CNT_DC_TERMS, terms);
+        count_add1(w.counters, CNT_DC_ROOTS, roots);
+        count_add1(w.counters, CNT_DC_LOW_PAIRS, pairs);
+        count_add1(w.counters, CNT_DC_ROW_PAIRS, pairs);
+        count_add1(w.counters, CNT_MERGE_COLS, c.mcols);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -520,16 +531,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
                      save_roots ? w.tau : nullptr, pk0, c);
     if (c.bad) atomicOr(w.status, ST_SEC_NOCONV);
     // the whole-merge workgroups' counters (the same work, counted alike)
-    count_add(w.counters, CNT_SEC_TERMS, c.terms);
-    count_add(w.counters, CNT_SWEEPS, c.sweeps);
-    count_add(w.counters, CNT_ROOTS, c.roots);
-    count_add(w.counters, CNT_LOW_PAIRS, c.lpairs);
-    count_add(w.counters, CNT_ROW_PAIRS, c.rpairs);
-    count_add(w.counters, CNT_LB_TERMS, c.terms);
-    count_add(w.counters, CNT_LB_LOW_PAIRS, c.lpairs);
-    count_add(w.counters, CNT_LB_ROW_PAIRS, c.rpairs);
-    count_add(w.counters, CNT_LB_ROOTS, c.roots);
-    count_add(w.counters, CNT_MERGE_COLS, c.mcols);
+    const unsigned terms = wave_sum_u32(c.terms), sweeps = wave_sum_u32(c.sweeps), roots = wave_sum_u32(c.roots),
+                   pairs = wave_sum_u32(c.pairs);
+    if (lane == 0) {
+        count_add1(w.counters, CNT_SEC_TERMS, terms);
+        count_add1(w.counters, CNT_SWEEPS, sweeps);
+        count_add1(w.counters, CNT_ROOTS, roots);
+        count_add1(w.counters, CNT_LOW_PAIRS, pairs);
+        count_add1(w.counters, CNT_ROW_PAIRS, pairs);
+        count_add1(w.counters, CNT_LB_TERMS, terms);
+        count_add1(w.counters, CNT_LB_LOW_PAIRS, pairs);
+        count_add1(w.counters, CNT_LB_ROW_PAIRS, pairs);
+        count_add1(w.counters, CNT_LB_ROOTS, roots);
+        count_add1(w.counters, CNT_MERGE_COLS, c.mcols);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -897,10 +912,6 @@ __device__ __forceinline__ int wide_merge_of(const int* witems, int M, int item)
     return __builtin_amdgcn_readfirstlane(lo);
 }
 
-struct WideSums {
-    double ps, dps, ph, dph, zz;
-};
-
 // Read-only views in the constant address space: a wave-uniform index into
 // them is a scalar load (s_load through the scalar data cache; these arrays
 // are written only by earlier launches, and nothing here is ever stored
@@ -910,40 +921,18 @@ typedef const __attribute__((address_space(4))) int cint;
 __device__ __forceinline__ cdouble* as_const(const double* p) { return (cdouble*)p; }
 __device__ __forceinline__ cint* as_const(const int* p) { return (cint*)p; }
 
-// Secular sums over poles j in [a, b) (wave-uniform) for this lane's root:
-// left poles j < L1 into (ps, dps), right poles j >= R0 into (ph, dph); poles
-// in [L1, R0) are skipped.  [w0, w1) (wave-uniform) contains every lane's
-// [L1, R0); below it every pole is left for every lane, above it right.
-template <bool ZZ>
+// Secular sums over poles j in [a, b) (wave-uniform) for this lane's root; the
+// poles in [L1, R0) are left out.  [w0, w1) (wave-uniform) contains every
+// lane's [L1, R0), so only there the terms need a per-lane choice.
 __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b, int w0, int w1, double Do, double tau,
-                                           int L1, int R0, WideSums& s) {
+                                           int L1, int R0, SecSums& s) {
     const int e1 = min(b, w0);
-    _Pragma("unroll 4") for (int j = a; j < e1; ++j) {
-        const double r = rcp_nr((D[j] - Do) - tau);
-        const double t = W[j] * r;
-        s.ps += t;
-        s.dps = fma(t, r, s.dps);
-        if (ZZ) s.zz += W[j];
-    }
+    _Pragma("unroll 4") for (int j = a; j < e1; ++j) sec_term(D[j], W[j], Do, tau, &s);
     const int s2 = max(a, w0), e2 = min(b, w1);
-    for (int j = s2; j < e2; ++j) {
-        const double r = rcp_nr((D[j] - Do) - tau);
-        const double t = W[j] * r;
-        const double dt = t * r;
-        const bool lf = j < L1, rt = j >= R0;
-        s.ps += lf ? t : 0.0;
-        s.dps += lf ? dt : 0.0;
-        s.ph += rt ? t : 0.0;
-        s.dph += rt ? dt : 0.0;
-        if (ZZ) s.zz += W[j];
-    }
-    _Pragma("unroll 4") for (int j = max(a, w1); j < b; ++j) {
-        const double r = rcp_nr((D[j] - Do) - tau);
-        const double t = W[j] * r;
-        s.ph += t;
-        s.dph = fma(t, r, s.dph);
-        if (ZZ) s.zz += W[j];
-    }
+    const unsigned exw = (unsigned)(R0 - L1);
+    _Pragma("unroll 2") for (int j = s2; j < e2; ++j)
+        sec_term(D[j], weight_unless((unsigned)(j - L1) < exw, W[j]), Do, tau, &s);
+    _Pragma("unroll 4") for (int j = max(a, w1); j < b; ++j) sec_term(D[j], W[j], Do, tau, &s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1122,16 +1111,13 @@ __device__ __forceinline__ int wide_last_root(int K, const double* __restrict__ 
     sec_start_last(K, D, Z, rho, zz, r);
     const double Do = D[K - 1];
     for (int it = 1; it <= cap; ++it) {
-        double ps = 0.0, dps = 0.0;
-        _Pragma("unroll 4") for (int j = threadIdx.x; j < K - 1; j += NW * 64) {
-            const double q = rcp_nr((D[j] - Do) - r->tau);
-            const double t = W[j] * q;
-            ps += t;
-            dps = fma(t, q, dps);
-        }
-        ps = wide_total<NW>(ps, red);
-        dps = wide_total<NW>(dps, red);
-        if (sec_update(r, rho, ps, dps, 0.0, 0.0, -ps)) return it;
+        SecSums s{0.0, 0.0, 0.0, 0.0};
+        _Pragma("unroll 4") for (int j = threadIdx.x; j < K - 1; j += NW * 64) sec_term(D[j], W[j], Do, r->tau, &s);
+        s.t = wide_total<NW>(s.t, red);
+        s.dt = wide_total<NW>(s.dt, red);
+        s.at = -s.t;  // every pole lies to the left
+        s.adt = -s.dt;
+        if (sec_update(r, rho, s)) return it;
     }
     return -1;
 }
@@ -1199,43 +1185,44 @@ __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, 
             }
             const int nn = fw.n1 - fw.n0;
             const int a = fw.n0 + (int)((long long)nn * wv / NW), b = fw.n0 + (int)((long long)nn * (wv + 1) / NW);
-            double tot[4];
+            SecSums tot;
             auto sweep = [&](double Do, double tau, int L1, int R0) {
-                WideSums u{0.0, 0.0, 0.0, 0.0, 0.0};
-                wide_sweep<false>(Dc, Wc, a, b, w0, w1, Do, tau, L1, R0, u);
+                SecSums u{0.0, 0.0, 0.0, 0.0};
+                wide_sweep(Dc, Wc, a, b, w0, w1, Do, tau, L1, R0, u);
                 if (fw.far && wv < 2) {
                     double ds;
                     const double v = far_value(coef + wv * kFarFold, ((Do - fw.c) + tau) * fw.rh, &ds);
                     ds *= fw.rh;
-                    if (wv == 0) {
-                        u.ps += v;
-                        u.dps += ds;
-                    } else {
-                        u.ph += v;
-                        u.dph += ds;
-                    }
+                    u.t += v;
+                    u.dt += ds;
+                    u.at += (wv == 0) ? -v : v;
+                    u.adt += (wv == 0) ? -ds : ds;
                 }
-                R4(buf, 0, wv) = u.ps;
-                R4(buf, 1, wv) = u.dps;
-                R4(buf, 2, wv) = u.ph;
-                R4(buf, 3, wv) = u.dph;
+                R4(buf, 0, wv) = u.t;
+                R4(buf, 1, wv) = u.dt;
+                R4(buf, 2, wv) = u.at;
+                R4(buf, 3, wv) = u.adt;
                 __syncthreads();
-                for (int q = 0; q < 4; ++q) {
+                auto total = [&](int q) {
                     double x = 0.0;
                     for (int v = 0; v < NW; ++v) x += R4(buf, q, v);
-                    tot[q] = x;
-                }
+                    return x;
+                };
+                tot.t = total(0);
+                tot.dt = total(1);
+                tot.at = total(2);
+                tot.adt = total(3);
                 buf ^= 1;
             };
             // first sweep: bracket midpoint with origin kk
             sweep(D[kk], 0.5 * (D[kk + 1] - D[kk]), kk, kk + 2);
-            if (!done) done = sec_start_interior(k, D, Z, rho, tot[0], tot[1], tot[2], tot[3], &r);
+            if (!done) done = sec_start_interior(k, D, Z, rho, tot, &r);
             for (int it = 1; it <= w.sec_cap; ++it) {
                 if (__all(done)) break;  // the same in every wave
                 const int L1 = r.orgl ? kk : kk + 1;
                 const int R0 = r.orgl ? kk + 1 : kk + 2;
                 sweep(D[r.o], r.tau, L1, R0);
-                if (!done && sec_update(&r, rho, tot[0], tot[1], tot[2], tot[3], tot[2] - tot[0])) {
+                if (!done && sec_update(&r, rho, tot)) {
                     done = true;
                     its = it;
                 }
@@ -1721,17 +1708,18 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
                 tau = r.tau;
                 sec_split(r, kk, &L1, &R0);
             }
-            double sm[5];
-            sec_sweep<RedGroup<G>, true>(K, Dv, Wv, Do, tau, L1, R0, sub, G, sm);
+            SecSums sm;
+            double zz;
+            sec_sweep<RedGroup<G>, true>(K, Dv, Wv, Do, tau, L1, R0, sub, G, &sm, &zz);
             bool done = false;
             int used = 0;
             if (phase == 1) {
-                if (k < K - 1) done = sec_start_interior(k, Dv, Zg, rho, sm[0], sm[1], sm[2], sm[3], &r);
-                else sec_start_last(K, Dv, Zg, rho, sm[4], &r);
+                if (k < K - 1) done = sec_start_interior(k, Dv, Zg, rho, sm, &r);
+                else sec_start_last(K, Dv, Zg, rho, zz, &r);
                 phase = 2;
             } else {
                 ++it;
-                if (sec_update(&r, rho, sm[0], sm[1], sm[2], sm[3], sm[2] - sm[0])) {
+                if (sec_update(&r, rho, sm)) {
                     done = true;
                     used = it;
                 } else if (it >= w.sec_cap) {
@@ -1926,12 +1914,6 @@ __device__ __forceinline__ auto canon1(Part part, Op op) {
     return op(c0, c1);
 }
 
-struct Sums4 {
-    double a, b, c, d;
-};
-__device__ __forceinline__ Sums4 add4(const Sums4& x, const Sums4& y) {
-    return Sums4{x.a + y.a, x.b + y.b, x.c + y.c, x.d + y.d};
-}
 struct Sums3 {
     double a, b, c;
 };
@@ -1941,56 +1923,39 @@ __device__ __forceinline__ double mul1(double x, double y) { return x * y; }
 
 // sec_sweep with canonical partial sums (same per-term arithmetic): a group of
 // G = 4, 8 or 16 lanes, or one lane (G = 1).
-template <int G, bool ZZ>
+template <int G>
 __device__ __forceinline__ void sec_sweep_c(int K, const double* __restrict__ D, const double* __restrict__ W,
-                                            double Do, double tau, int L1, int R0, int sub, double* s) {
+                                            double Do, double tau, int L1, int R0, int sub, SecSums* s) {
+    const unsigned exw = (unsigned)(R0 - L1);
     if constexpr (G == 1) {
-        static_assert(!ZZ, "one-lane sweeps sum z^2 separately");
-        const unsigned exw = (unsigned)(R0 - L1);
-        const Sums4 r = canon1(
+        *s = canon1(
             [&](int q) {
-                Sums4 a{0.0, 0.0, 0.0, 0.0};
-                for (int j = q; j < K; j += 16) {
-                    const double wr = W[j];
-                    const double rr = rcp_nr((D[j] - Do) - tau);
-                    const double wj = ((unsigned)(j - L1) < exw) ? 0.0 : wr;
-                    const double t = wj * rr;
-                    const double tl = fmin(t, 0.0), th = fmax(t, 0.0);
-                    a.a += tl;
-                    a.b = fma(tl, rr, a.b);
-                    a.c += th;
-                    a.d = fma(th, rr, a.d);
-                }
+                SecSums a{0.0, 0.0, 0.0, 0.0};
+                for (int j = q; j < K; j += 16)
+                    sec_term(D[j], weight_unless((unsigned)(j - L1) < exw, W[j]), Do, tau, &a);
                 return a;
             },
-            add4);
-        s[0] = r.a;
-        s[1] = r.b;
-        s[2] = r.c;
-        s[3] = r.d;
+            [](const SecSums& x, const SecSums& y) {
+                return SecSums{x.t + y.t, x.dt + y.dt, x.at + y.at, x.adt + y.adt};
+            });
     } else {
         constexpr int M = Canon<G>::M;
-        double ps[M], dps[M], ph[M], dph[M], zz[M];
+        SecSums a[M];
 #pragma unroll
-        for (int q = 0; q < M; ++q) ps[q] = dps[q] = ph[q] = dph[q] = zz[q] = 0.0;
-        const unsigned exw = (unsigned)(R0 - L1);
+        for (int q = 0; q < M; ++q) a[q] = SecSums{0.0, 0.0, 0.0, 0.0};
         canon_for<G>(K, sub, [&](int q, int j) {
-            const double wr = W[j];
-            const double rr = rcp_nr((D[j] - Do) - tau);
-            const double wj = ((unsigned)(j - L1) < exw) ? 0.0 : wr;
-            const double t = wj * rr;
-            const double tl = fmin(t, 0.0), th = fmax(t, 0.0);
-            ps[q] += tl;
-            dps[q] = fma(tl, rr, dps[q]);
-            ph[q] += th;
-            dph[q] = fma(th, rr, dph[q]);
-            if (ZZ) zz[q] += wr;
+            sec_term(D[j], weight_unless((unsigned)(j - L1) < exw, W[j]), Do, tau, &a[q]);
         });
-        s[0] = Canon<G>::sum(ps);
-        s[1] = Canon<G>::sum(dps);
-        s[2] = Canon<G>::sum(ph);
-        s[3] = Canon<G>::sum(dph);
-        if (ZZ) s[4] = Canon<G>::sum(zz);
+        auto total = [&](auto field) {
+            double p[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q) p[q] = field(a[q]);
+            return Canon<G>::sum(p);
+        };
+        s->t = total([](const SecSums& x) { return x.t; });
+        s->dt = total([](const SecSums& x) { return x.dt; });
+        s->at = total([](const SecSums& x) { return x.at; });
+        s->adt = total([](const SecSums& x) { return x.adt; });
     }
 }
 
@@ -2028,10 +1993,10 @@ __device__ __forceinline__ int secular_root_c(int k, int K, const double* __rest
     }
     const int kk = (k < K - 1) ? k : K - 2;
     SecRoot r;
-    double s[5];
+    SecSums s;
     if (k < K - 1) {
-        sec_sweep_c<G, false>(K, D, W, D[kk], 0.5 * (D[kk + 1] - D[kk]), kk, kk + 2, sub, s);
-        if (sec_start_interior(k, D, Z, rho, s[0], s[1], s[2], s[3], &r)) {
+        sec_sweep_c<G>(K, D, W, D[kk], 0.5 * (D[kk + 1] - D[kk]), kk, kk + 2, sub, &s);
+        if (sec_start_interior(k, D, Z, rho, s, &r)) {
             *org_out = r.o;
             *tau_out = r.tau;
             return 0;
@@ -2042,8 +2007,8 @@ __device__ __forceinline__ int secular_root_c(int k, int K, const double* __rest
     for (int it = 1; it <= cap; ++it) {
         int L1, R0;
         sec_split(r, kk, &L1, &R0);
-        sec_sweep_c<G, false>(K, D, W, D[r.o], r.tau, L1, R0, sub, s);
-        if (sec_update(&r, rho, s[0], s[1], s[2], s[3], s[2] - s[0])) {
+        sec_sweep_c<G>(K, D, W, D[r.o], r.tau, L1, R0, sub, &s);
+        if (sec_update(&r, rho, s)) {
             *org_out = r.o;
             *tau_out = r.tau;
             return it;
@@ -2182,9 +2147,9 @@ __device__ void wave_roots_canon(const MergeRec* smr, int K, const double* __res
             wl.org[g] = o;
             wl.tau[g] = tau;
             wl.rootval[g] = D[o] + tau;
-            const unsigned long long sw = (sp.K > 1) ? (unsigned long long)((it < 0 ? wl.sec_cap : it) + 1) : 0ULL;
+            const unsigned sw = (sp.K > 1) ? (unsigned)((it < 0 ? wl.sec_cap : it) + 1) : 0u;
             c.sweeps += sw;
-            c.terms += sw * (unsigned long long)sp.K;
+            c.terms += sw * (unsigned)sp.K;
             c.roots += 1;
             if (corg) {
                 const long long gp = pk0 + R.pk + (g - sp.ks);
@@ -2204,7 +2169,7 @@ __device__ void wave_roots_canon(const MergeRec* smr, int K, const double* __res
                                         wl.tau + sp.ks, rho, sub);
         if (sub == 0) {
             wl.zhat[g] = zh;
-            c.lpairs += (unsigned long long)sp.K;
+            c.pairs += (unsigned)sp.K;
         }
     }
     __syncthreads();
@@ -2218,7 +2183,6 @@ __device__ void wave_roots_canon(const MergeRec* smr, int K, const double* __res
         if (sub == 0) {
             wl.PBL[g] = bl;
             wl.PBH[g] = bh;
-            c.rpairs += (unsigned long long)sp.K;
         }
     }
     __syncthreads();
@@ -2232,7 +2196,7 @@ __device__ __forceinline__ void small_merge_body(const MergeRec& R, int K, long 
                                                  double* sL, double* sR, int* sO, int cbase) {
     const int sub = threadIdx.x % G, grp = threadIdx.x / G, ng = NT / G;
     int bad = 0;
-    unsigned long long terms = 0, sweeps = 0, roots = 0, pairs = 0;
+    unsigned sweeps = 0;
     for (int k = grp; k < K; k += ng) {
         int o;
         double tau;
@@ -2241,10 +2205,7 @@ __device__ __forceinline__ void small_merge_body(const MergeRec& R, int K, long 
         if (sub == 0) {
             sO[k] = o;
             sT[k] = tau;
-            const unsigned long long sw = (K > 1) ? (unsigned long long)((it < 0 ? w.sec_cap : it) + 1) : 0ULL;
-            sweeps += sw;
-            terms += sw * (unsigned long long)K;
-            roots += 1;
+            if (K > 1) sweeps += (unsigned)((it < 0 ? w.sec_cap : it) + 1);
         }
     }
     __syncthreads();
@@ -2259,7 +2220,6 @@ __device__ __forceinline__ void small_merge_body(const MergeRec& R, int K, long 
             if (sub == 0) {
                 sH[i] = zh;
                 w.zhat[ks + i] = zh;
-                pairs += (unsigned long long)K;
             }
         }
         __syncthreads();
@@ -2273,15 +2233,26 @@ __device__ __forceinline__ void small_merge_body(const MergeRec& R, int K, long 
         }
     }
     if (bad && sub == 0) atomicOr(w.status, ST_SEC_NOCONV);
-    count_add(w.counters, CNT_SEC_TERMS, terms);
-    count_add(w.counters, CNT_SWEEPS, sweeps);
-    count_add(w.counters, CNT_ROOTS, roots);
-    count_add(w.counters, CNT_LOW_PAIRS, pairs);
-    count_add(w.counters, CNT_ROW_PAIRS, pairs);
-    count_add(w.counters, cbase, terms);
-    count_add(w.counters, cbase + 1, pairs);
-    count_add(w.counters, cbase + 2, pairs);
-    count_add(w.counters, cbase + 3, roots);
+    // counters: the waves' sweeps are summed (every sweep is K terms), the
+    // rest follows from K (nine sums per wave of their own cost about 1.5 us
+    // at the end of every merge)
+    const unsigned long long sw = wave_sum_u32(sweeps);
+    if ((threadIdx.x & 63) == 0 && sw) {
+        count_add1(w.counters, CNT_SWEEPS, sw);
+        count_add1(w.counters, CNT_SEC_TERMS, sw * (unsigned long long)K);
+        count_add1(w.counters, cbase, sw * (unsigned long long)K);
+    }
+    if (threadIdx.x == 0) {
+        const unsigned long long kk = (unsigned long long)K * (unsigned long long)K;
+        count_add1(w.counters, CNT_ROOTS, (unsigned long long)K);
+        count_add1(w.counters, cbase + 3, (unsigned long long)K);
+        if (!(R.flags & MF_ROOT) || w.rows_out) {
+            count_add1(w.counters, CNT_LOW_PAIRS, kk);
+            count_add1(w.counters, CNT_ROW_PAIRS, kk);
+            count_add1(w.counters, cbase + 1, kk);
+            count_add1(w.counters, cbase + 2, kk);
+        }
+    }
 }
 
 // LDS staging of one merge's active arrays for the fused root steps (room
