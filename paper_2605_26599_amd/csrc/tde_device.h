@@ -121,11 +121,12 @@ TDE_DEV double merge_tol(const double* __restrict__ D, long long pk, int s) {
 
 // Close-pole test for consecutive poles a < b (Section 4.1, deflation): the
 // Givens rotation that zeroes z_a drops an off-diagonal (D_b - D_a) c s.
+// With c = zb/t, s = za/t, t^2 = za^2 + zb^2 it is multiplied out, which takes
+// no root and no division (|z| <= 1, and non-negligible z are far above the
+// square root of the smallest number).
 TDE_DEV bool close_pair(double Da, double za, double Db, double zb, double tol) {
 #pragma clang fp contract(off)
-    double t = hypot(za, zb);
-    double c = zb / t, s = za / t;
-    return fabs((Db - Da) * c * s) <= tol;
+    return fabs((Db - Da) * (za * zb)) <= tol * (za * za + zb * zb);
 }
 
 // ---------------------------------------------------------------------------
@@ -853,78 +854,98 @@ TDE_DEV bool run_step(RunState* cur, const RunState& nx, double tol, RunState* d
 // so runs proceed in parallel without races; a candidate outside every run is
 // copied through by its own thread.  on_rotate(p) is called for each column
 // rotated away.
+// The merged columns a run reads, the candidates' positions, and where the
+// rotated columns and their states go.
+struct RunArrays {
+    const int* __restrict__ nnpos;
+    const double *D, *Z, *L, *H;
+    double *D2, *Z2, *L2, *H2;
+    int* st;
+};
+
+TDE_DEV bool cand_close(const RunArrays& v, long long a, long long b, double tol) {
+    const long long pa = v.nnpos[a], pb = v.nnpos[b];
+    return close_pair(v.D[pa], v.Z[pa], v.D[pb], v.Z[pb], tol);
+}
+
 TDE_DEV bool cand_close(const Work& w, long long a, long long b, double tol) {
     const long long pa = w.nnpos[a], pb = w.nnpos[b];
     return close_pair(w.D[pa], w.Z[pa], w.D[pb], w.Z[pb], tol);
 }
 
+// Candidate g of a merge whose candidates are [gs, ge).
 template <class OnRotate>
-TDE_DEV void body_runs(long long g, int m, const MergeRec* __restrict__ mr, const Work& w, OnRotate on_rotate) {
-    const int* __restrict__ nnpos = w.nnpos;
+TDE_DEV void runs_from(long long g, long long gs, long long ge, double tol, const RunArrays& v, OnRotate on_rotate) {
+    const int* __restrict__ nnpos = v.nnpos;
     const long long t = nnpos[g];
-    const MergeRec R = mr[m];
-    const int s = R.nL + R.nR;
-    const long long gs = w.scanC[R.pk], ge = w.scanC[R.pk + s];
-    const double tol = merge_tol(w.D, R.pk, s);
-    const bool cl_next = (g + 1 < ge) && cand_close(w, g, g + 1, tol);
-    const bool cl_prev = (g > gs) && cand_close(w, g - 1, g, tol);
+    const bool cl_next = (g + 1 < ge) && cand_close(v, g, g + 1, tol);
+    const bool cl_prev = (g > gs) && cand_close(v, g - 1, g, tol);
     if (cl_prev) return;  // inside a run owned by an earlier candidate
     if (!cl_next) {       // not in any run: copy through
-        w.D2[t] = w.D[t];
-        w.Z2[t] = w.Z[t];
-        w.RL2[t] = w.RL[t];
-        w.RH2[t] = w.RH[t];
+        v.D2[t] = v.D[t];
+        v.Z2[t] = v.Z[t];
+        v.L2[t] = v.L[t];
+        v.H2[t] = v.H[t];
         return;
     }
     long long r = g + 1;
-    while (r + 1 < ge && cand_close(w, r, r + 1, tol)) ++r;
+    while (r + 1 < ge && cand_close(v, r, r + 1, tol)) ++r;
     long long pc = t;
-    RunState cur{w.D[pc], w.Z[pc], w.RL[pc], w.RH[pc]};
+    RunState cur{v.D[pc], v.Z[pc], v.L[pc], v.H[pc]};
     for (long long j = g + 1; j <= r; ++j) {
         const long long pj = nnpos[j];
-        const RunState nx{w.D[pj], w.Z[pj], w.RL[pj], w.RH[pj]};
+        const RunState nx{v.D[pj], v.Z[pj], v.L[pj], v.H[pj]};
         RunState def;
         double c, sn;
         if (run_step(&cur, nx, tol, &def, &c, &sn)) {
-            w.D2[pc] = def.D;
-            w.Z2[pc] = 0.0;
-            w.RL2[pc] = def.L;
-            w.RH2[pc] = def.H;
-            w.st[pc] = 2;
+            v.D2[pc] = def.D;
+            v.Z2[pc] = 0.0;
+            v.L2[pc] = def.L;
+            v.H2[pc] = def.H;
+            v.st[pc] = 2;
             on_rotate(pc);
         } else {
-            w.D2[pc] = cur.D;
-            w.Z2[pc] = cur.Z;
-            w.RL2[pc] = cur.L;
-            w.RH2[pc] = cur.H;
+            v.D2[pc] = cur.D;
+            v.Z2[pc] = cur.Z;
+            v.L2[pc] = cur.L;
+            v.H2[pc] = cur.H;
             cur = nx;
         }
         pc = pj;
     }
-    w.D2[pc] = cur.D;
-    w.Z2[pc] = cur.Z;
-    w.RL2[pc] = cur.L;
-    w.RH2[pc] = cur.H;
+    v.D2[pc] = cur.D;
+    v.Z2[pc] = cur.Z;
+    v.L2[pc] = cur.L;
+    v.H2[pc] = cur.H;
     // The rotated-away columns of a run join their own list, ascending in
     // position order: sort them among the run's rotated positions (only
     // columns g..r-1 can be rotated away).  Their values lie in [D_g, D_r],
     // so the lists of different runs stay ordered.
     for (long long j = g; j < r; ++j) {
         const long long pj = nnpos[j];
-        if (w.st[pj] != 2) continue;
-        const double kD = w.D2[pj], kL = w.RL2[pj], kH = w.RH2[pj];
+        if (v.st[pj] != 2) continue;
+        const double kD = v.D2[pj], kL = v.L2[pj], kH = v.H2[pj];
         long long h = j;
         for (long long q = j - 1; q >= g; --q) {
             const long long pq = nnpos[q];
-            if (w.st[pq] != 2) continue;
-            if (w.D2[pq] <= kD) break;
+            if (v.st[pq] != 2) continue;
+            if (v.D2[pq] <= kD) break;
             const long long ph = nnpos[h];
-            w.D2[ph] = w.D2[pq]; w.RL2[ph] = w.RL2[pq]; w.RH2[ph] = w.RH2[pq];
+            v.D2[ph] = v.D2[pq]; v.L2[ph] = v.L2[pq]; v.H2[ph] = v.H2[pq];
             h = q;
         }
         const long long ph = nnpos[h];
-        w.D2[ph] = kD; w.RL2[ph] = kL; w.RH2[ph] = kH;
+        v.D2[ph] = kD; v.L2[ph] = kL; v.H2[ph] = kH;
     }
+}
+
+template <class OnRotate>
+TDE_DEV void body_runs(long long g, int m, const MergeRec* __restrict__ mr, const Work& w, OnRotate on_rotate) {
+    const MergeRec R = mr[m];
+    const int s = R.nL + R.nR;
+    const long long gs = w.scanC[R.pk], ge = w.scanC[R.pk + s];
+    const RunArrays v{w.nnpos, w.D, w.Z, w.RL, w.RH, w.D2, w.Z2, w.RL2, w.RH2, w.st};
+    runs_from(g, gs, ge, merge_tol(w.D, R.pk, s), v, on_rotate);
 }
 
 // Largest m with scan[mr[m].pk] <= g: the merge owning active column g.

@@ -2336,25 +2336,20 @@ __global__ __launch_bounds__(NT) void k_small_merge(const MergeRec* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Levels whose merges all have at most kFuseMax columns (outside checkpoint
-// mode): one workgroup per merge runs the whole merge -- merged order and z~,
-// negligible-z flags, close-pole runs, the three-way split, roots, Loewner z,
-// rows and the assembly -- with barriers between the steps instead of kernel
-// boundaries and merge-local prefix counts instead of level-wide scans: one
-// launch per level instead of six.  The per-column and per-root device
-// functions are those of the level-wide kernels; they see the merge's active
-// and rotated lists and its candidate list through views that start at the
-// merge's packed position pk (a merge's lists never outgrow its own range),
-// while the negligible list is indexed by pk itself, as body_assemble reads it
-// with local counts.  The prefix arrays are shifted by one slot per merge so
-// that neighbouring merges' counts (s + 1 entries each) do not overlap.
+// Levels whose merges all have at most kFuseMax columns: one workgroup per
+// merge runs the whole merge -- merged order and z~, negligible-z flags,
+// close-pole runs, the three-way split, roots, Loewner z, rows and the
+// assembly -- with barriers between the steps instead of kernel boundaries:
+// one launch per level instead of six.  The arithmetic is that of the
+// level-wide kernels (the same per-column and per-root device functions where
+// they take their arrays as arguments).
 // ---------------------------------------------------------------------------
 // Above this many merges a level keeps the level-wide kernels: they stream the
 // columns with all lanes busy, while a workgroup per merge would queue
 // thousands of mostly idle 512-thread groups (a merge's result is the same
 // either way).
 // Levels of merges of at most kLevelBlockSmallCols columns always take them:
-// their workgroups are sized to the merge (64 or 128 threads, a few KB of
+// their workgroups are sized to the merge (64 or 128 threads, 5 or 9 KB of
 // LDS), so even tens of thousands of them do not crowd the compute units.
 constexpr int kLevelBlockMaxMerges = 1024;
 #ifndef TDE_LEVEL_BLOCK_SMALL_COLS
@@ -2378,113 +2373,233 @@ static bool level_blocked(const LevelInfo& L) {
     return level_waved(L) || (L.smax <= kFuseMax && (L.M <= kLevelBlockMaxMerges || L.smax <= kLevelBlockSmallCols));
 }
 
-template <int NT, int CAP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_level_block(
-    const MergeRec* __restrict__ mr, const double* __restrict__ e,
-                                                    const unsigned long long* __restrict__ pmax, Work w,
-                                                    double* __restrict__ out, int gmax) {
-    if (input_nonfinite(w)) return;
-    __shared__ MergeRec sm[1];
-    __shared__ int wsum[16];
-    __shared__ SmallStageT<CAP> sg;
-    const MergeRec R = mr[blockIdx.x];
-    if (threadIdx.x == 0) sm[0] = R;
-    const int s = R.nL + R.nR;
-    const long long pk = R.pk;
-    Work v = w;
-    // merge b's counts live at [pk + b, pk + b + s]: its total (index pk + s of
-    // the view) must not land on the next merge's first count
-    v.scan = w.scan + blockIdx.x;
-    v.scanC = w.scanC + blockIdx.x;
-    v.scanR = w.scanR + blockIdx.x;
-    v.nnpos = w.nnpos + pk;
-    v.Da = w.Da + pk;
-    v.Za = w.Za + pk;
-    v.Wa = w.Wa + pk;
-    v.RLa = w.RLa + pk;
-    v.RHa = w.RHa + pk;
-    v.org = w.org + pk;
-    v.tau = w.tau + pk;
-    v.rootval = w.rootval + pk;
-    v.zhat = w.zhat + pk;
-    v.PBL = w.PBL + pk;
-    v.PBH = w.PBH + pk;
-    v.Dr = w.Dr + pk;
-    v.RLr = w.RLr + pk;
-    v.RHr = w.RHr + pk;
+// LDS of one merge of at most CAP columns.  Before the three-way split: the
+// merged columns (D, Z, RL, RH), their states, the candidates' positions and
+// the columns after the close-pole rotations (D2, Z2, RL2, RH2; the children's
+// spectra are merged from D2's place).  Each thread then takes its column into
+// registers, and the same arrays hold the three lists back to back (roots'
+// poles first, then rotated, then negligible columns: D, L, H), the active z
+// and z^2, tau, z-hat and the root values; the roots' parent rows replace z
+// and z^2 when those have been read for the last time.
+template <int CAP>
+struct LevelLds {
+    double a[8][CAP];
+    int st[CAP], nn[CAP];
+    int cnt[3][16];
+};
+
+// Rank of this thread's flag among the workgroup's and the total (NT threads,
+// one flag each): ballots within the waves, their counts through LDS.
+template <int NT>
+__device__ __forceinline__ int flag_rank(bool f, int* cnt, int* total) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const unsigned long long m = __ballot(f);
+    if (lane == 0) cnt[wv] = (int)__popcll(m);
     __syncthreads();
-    // merged order, z~, negligible-z flags
-    for (int i = threadIdx.x; i < s; i += NT) {
-        int f;
-        body_merge(pk + i, 0, sm, e, pmax, v, &f);
+    int before = 0, all = 0;
+#pragma unroll
+    for (int v = 0; v < NT / 64; ++v) {
+        const int c = cnt[v];
+        before += (v < wv) ? c : 0;
+        all += c;
     }
-    __syncthreads();
-    // candidates: merge-local prefix counts and positions (each thread a run
-    // of consecutive columns)
-    const int cs = (s + NT - 1) / NT;
-    const int c0 = min(s, (int)threadIdx.x * cs), c1 = min(s, c0 + cs);
-    int cnt = 0;
-    for (int i = c0; i < c1; ++i) cnt += (v.st[pk + i] == 1) ? 1 : 0;
-    const int incl = block_incl_scan(cnt, wsum);
-    int g = incl - cnt;
-    for (int i = c0; i < c1; ++i) {
-        v.scanC[pk + i] = g;
-        if (v.st[pk + i] == 1) v.nnpos[g++] = (int)(pk + i);
-    }
-    if (threadIdx.x == NT - 1) v.scanC[pk + s] = incl;
-    __syncthreads();
-    // close-pole runs
-    const int nc = v.scanC[pk + s];
-    for (int q = threadIdx.x; q < nc; q += NT) body_runs(q, 0, sm, v, [](long long) {});
-    __syncthreads();
-    // three-way split
-    int ca = 0, cr = 0;
-    for (int i = c0; i < c1; ++i) {
-        const int st = v.st[pk + i];
-        ca += (st == 1) ? 1 : 0;
-        cr += (st == 2) ? 1 : 0;
-    }
-    const int ia = block_incl_scan(ca, wsum);
-    __syncthreads();
-    const int ir = block_incl_scan(cr, wsum);
-    int ga = ia - ca, gr = ir - cr;
-    for (int i = c0; i < c1; ++i) {
-        const long long t = pk + i;
-        const int st = v.st[t];
-        v.scan[t] = ga;
-        v.scanR[t] = gr;
-        if (st == 1) {
-            const double z = v.Z2[t];
-            v.Da[ga] = v.D2[t];
-            v.Za[ga] = z;
-            v.Wa[ga] = z * z;
-            v.RLa[ga] = v.RL2[t];
-            v.RHa[ga] = v.RH2[t];
-            ++ga;
-        } else if (st == 2) {
-            v.Dr[gr] = v.D2[t];
-            v.RLr[gr] = v.RL2[t];
-            v.RHr[gr] = v.RH2[t];
-            ++gr;
-        } else {
-            const long long q = pk + (i - ga - gr);
-            v.Dd[q] = v.D[t];
-            v.RLd[q] = v.RL[t];
-            v.RHd[q] = v.RH[t];
+    *total = all;
+    return before + (int)__popcll(m & ((1ULL << lane) - 1ULL));
+}
+
+// Roots, z-hat and parent rows of a merge in LDS, G lanes per root or pole.
+template <int NT, int G, int CAP>
+__device__ __forceinline__ void level_roots(LevelLds<CAP>& sh, const MergeRec& R, int K, double rho, const Work& w) {
+    const int sub = threadIdx.x % G, grp = threadIdx.x / G, ng = NT / G;
+    double *sD = sh.a[4], *sL = sh.a[6], *sH = sh.a[7], *sZ = sh.a[5], *sW = sh.a[0], *sT = sh.a[1], *sh_ = sh.a[2],
+           *rv = sh.a[3];
+    int* sO = sh.st;
+    int bad = 0;
+    unsigned sweeps = 0;
+    for (int k = grp; k < K; k += ng) {
+        int o;
+        double tau;
+        const int it = secular_root_c<G>(k, K, sD, sZ, sW, rho, sub, w.sec_cap, &o, &tau);
+        if (it < 0) bad = 1;
+        if (sub == 0) {
+            sO[k] = o;
+            sT[k] = tau;
+            rv[k] = sD[o] + tau;
+            if (K > 1) sweeps += (unsigned)((it < 0 ? w.sec_cap : it) + 1);
         }
     }
-    if (threadIdx.x == NT - 1) {
-        v.scan[pk + s] = ia;
-        v.scanR[pk + s] = ir;
+    if (bad && sub == 0) atomicOr(w.status, ST_SEC_NOCONV);
+    const unsigned sw = wave_sum_u32(sweeps);
+    if ((threadIdx.x & 63) == 0 && sw) {
+        count_add1(w.counters, CNT_SWEEPS, sw);
+        count_add1(w.counters, CNT_SEC_TERMS, (unsigned long long)sw * (unsigned long long)K);
+        count_add1(w.counters, CNT_LB_TERMS, (unsigned long long)sw * (unsigned long long)K);
     }
     __syncthreads();
-    // roots, Loewner z, rows
-    const int K = v.scan[pk + s];
-    if (K >= 1) small_merge_solve<NT>(R, K, 0, e, pmax, v, sg, CNT_LB_TERMS, gmax);
+    if (!(R.flags & MF_ROOT) || w.rows_out) {
+        for (int i = grp; i < K; i += ng) {
+            const double zh = lowner_z_c<G>(i, K, sD, sZ, sO, sT, rho, sub);
+            if (sub == 0) sh_[i] = zh;
+        }
+        __syncthreads();
+        for (int k = grp; k < K; k += ng) {
+            double bl, bh;
+            root_rows_c<G>(K, sD, sh_, sL, sH, sO[k], sT[k], sub, &bl, &bh);
+            if (sub == 0) {
+                sh.a[5][k] = bl;
+                sh.a[0][k] = bh;
+            }
+        }
+    }
+}
+
+// One thread per column (NT >= CAP >= s), every array of the merge in LDS: the
+// children's columns are read once and the parent's written once, and a step
+// costs LDS latencies instead of stores and loads through L2, which took 9.5 to
+// 13.7 us of every merge (n = 300, leaves of 8: the six levels 184 -> 102 us;
+// uniform n = 65536: the 128-, 256- and 512-column levels 212 -> 130 us).
+// Bound by the roots: chains of sweeps, issue-bound where a level fills its
+// compute units.  save_roots: keep the roots as (origin, offset) at the merge's
+// packed positions (checkpointing forward).
+template <int NT, int CAP>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_level_block(
+    const MergeRec* __restrict__ mr, const double* __restrict__ e, const unsigned long long* __restrict__ pmax, Work w,
+    double* __restrict__ out, int gmax, int save_roots) {
+    static_assert(NT >= CAP && NT <= 1024, "one thread per column");
+    if (input_nonfinite(w)) return;
+    __shared__ LevelLds<CAP> sh;
+    const MergeRec R = mr[blockIdx.x];
+    const int t = threadIdx.x, s = R.nL + R.nR;
+    const bool col = t < s;
+    double x = 0.0, lo = 0.0, hi = 0.0;
+    if (col) {
+        x = w.lam[R.off + t];
+        lo = w.blo[R.off + t];
+        hi = w.bhi[R.off + t];
+    }
+    double xl = 0.0, xh = 0.0;
+    if (w.xmode && col) {
+        // requested rows: a row reaches this merge from the child that holds it
+        const bool left = t < R.nL;
+        const long long mid = R.off + R.nL, end = mid + R.nR;
+        if (w.xa_row >= R.off && w.xa_row < end && (w.xa_row < mid) == left) xl = w.xa[R.off + t];
+        if (w.xb_row >= R.off && w.xb_row < end && (w.xb_row < mid) == left) xh = w.xb[R.off + t];
+    }
+    double sgn;
+    const double rho = merge_rho(R, e, pmax, &sgn);
+    double *D = sh.a[0], *Z = sh.a[1], *RL = sh.a[2], *RH = sh.a[3];
+    double* lam = sh.a[4];
+    if (col) lam[t] = x;
     __syncthreads();
-    // the parent's spectrum and rows, or the problem's eigenvalues
-    for (int i = threadIdx.x; i < s; i += NT) body_assemble(pk + i, 0, sm, pmax, v, out);
-    if (threadIdx.x == 0) count_add1(w.counters, CNT_MERGE_COLS, (unsigned long long)s);
+    // merged order, z~, outer rows, negligible-z flags (merge_emit)
+    const double tol = 8.0 * DBL_EPSILON * fmax(fmax(fmax(fabs(lam[0]), fabs(lam[R.nL - 1])),
+                                                     fmax(fabs(lam[R.nL]), fabs(lam[s - 1]))), 1.0);
+    if (col) {
+        const double rs2 = 0.70710678118654752440;  // 1/sqrt(2)
+        const bool left = t < R.nL;
+        const int P = left ? t + count_lt<true>(lam + R.nL, R.nR, x) : t - R.nL + count_le<true>(lam, R.nL, x);
+        const double z = left ? hi * rs2 : sgn * lo * rs2;
+        D[P] = x;
+        Z[P] = z;
+        RL[P] = w.xmode ? xl : (left ? lo : 0.0);
+        RH[P] = w.xmode ? xh : (left ? 0.0 : hi);
+        sh.st[P] = (rho * fabs(z) > tol) ? 1 : 0;
+    }
+    __syncthreads();
+    // candidates and close-pole runs
+    const bool f = col && sh.st[t] != 0;
+    int nc;
+    const int g0 = flag_rank<NT>(f, sh.cnt[0], &nc);
+    if (f) sh.nn[g0] = t;
+    __syncthreads();
+    const RunArrays ra{sh.nn, D, Z, RL, RH, sh.a[4], sh.a[5], sh.a[6], sh.a[7], sh.st};
+    if (t < nc) runs_from(t, 0, nc, tol, ra, [](long long) {});
+    __syncthreads();
+    // three-way split
+    const int st = col ? sh.st[t] : 3;
+    double vd = 0.0, vz = 0.0, vl = 0.0, vh = 0.0;
+    if (st == 0) {
+        vd = D[t];
+        vl = RL[t];
+        vh = RH[t];
+    } else if (st < 3) {
+        vd = sh.a[4][t];
+        vz = sh.a[5][t];
+        vl = sh.a[6][t];
+        vh = sh.a[7][t];
+    }
+    int K, nr;
+    const int g = flag_rank<NT>(st == 1, sh.cnt[1], &K);
+    const int gr = flag_rank<NT>(st == 2, sh.cnt[2], &nr);
+    if (col) {
+        const int q = st == 1 ? g : (st == 2 ? K + gr : K + nr + (t - g - gr));
+        sh.a[4][q] = vd;
+        sh.a[6][q] = vl;
+        sh.a[7][q] = vh;
+        if (st == 1) {
+            sh.a[5][q] = vz;
+            sh.a[0][q] = vz * vz;
+        }
+    }
+    __syncthreads();
+    // roots, Loewner z, rows (lanes per root as in the fused merges)
+    const int gk = (K * 16 <= 1024) ? 16 : ((K * 8 <= 1024) ? 8 : 4);
+    const int G = gk < gmax ? gk : gmax;
+    if (K > 0) {
+        if (G >= 16) level_roots<NT, 16>(sh, R, K, rho, w);
+        else if (G >= 8) level_roots<NT, 8>(sh, R, K, rho, w);
+        else level_roots<NT, 4>(sh, R, K, rho, w);
+    }
+    __syncthreads();
+    // the parent's spectrum and rows, or the problem's eigenvalues: merge of
+    // the three ascending lists (ties: roots, rotated, negligible)
+    if (col) {
+        const int nn = s - K - nr;
+        const double *rv = sh.a[3], *Dr = sh.a[4] + K, *Dd = sh.a[4] + K + nr;
+        const bool isroot = t < K;
+        const double val = isroot ? rv[t] : sh.a[4][t];
+        int pos;
+        if (isroot) pos = t + count_lt<true>(Dr, nr, val) + count_lt<true>(Dd, nn, val);
+        else if (t < K + nr) pos = t - K + count_le<true>(rv, K, val) + count_lt<true>(Dd, nn, val);
+        else pos = t - K - nr + count_le<true>(rv, K, val) + count_le<true>(Dr, nr, val);
+        const double bl = isroot ? sh.a[5][t] : sh.a[6][t], bh = isroot ? sh.a[0][t] : sh.a[7][t];
+        const long long P = R.off + pos;
+        const bool top = (R.flags & MF_ROOT) != 0;
+        if (w.xmode) {
+            const bool ha = w.xa_row >= R.off && w.xa_row < R.off + s;
+            const bool hb = w.xb_row >= R.off && w.xb_row < R.off + s;
+            if (top) {
+                if (ha && w.xq_a) w.xq_a[P] = bl;
+                if (hb && w.xq_b) w.xq_b[P] = bh;
+            } else {
+                if (ha) w.xa[P] = bl;
+                if (hb) w.xb[P] = bh;
+            }
+        } else if (top) {
+            out[P] = val * scale_of(pmax[R.prob]);
+            if (w.rows_out) store_rows(w, P, bl, bh);
+        } else {
+            w.lam[P] = val;
+            w.blo[P] = bl;
+            w.bhi[P] = bh;
+        }
+        if (save_roots && isroot) {
+            w.org[R.pk + t] = sh.st[t];
+            w.tau[R.pk + t] = sh.a[1][t];
+        }
+    }
+    if (t == 0) {
+        const unsigned long long kk = (unsigned long long)K * (unsigned long long)K;
+        count_add1(w.counters, CNT_MERGE_COLS, (unsigned long long)s);
+        count_add1(w.counters, CNT_ROOTS, (unsigned long long)K);
+        count_add1(w.counters, CNT_LB_ROOTS, (unsigned long long)K);
+        if (!(R.flags & MF_ROOT) || w.rows_out) {
+            count_add1(w.counters, CNT_LOW_PAIRS, kk);
+            count_add1(w.counters, CNT_ROW_PAIRS, kk);
+            count_add1(w.counters, CNT_LB_LOW_PAIRS, kk);
+            count_add1(w.counters, CNT_LB_ROW_PAIRS, kk);
+        }
+    }
 }
 
 template <int G, bool WithRoot, bool Wide>
@@ -3113,24 +3228,32 @@ constexpr int kLevelBlockWideMerges = 256;
 
 // Whole merges in one workgroup each: 512 threads on other levels of few
 // merges (each merge's chain of steps is latency-bound, so more threads per
-// merge shorten it), else a workgroup sized to the level's largest merge
-// (levels of many merges are throughput-bound).
+// merge shorten it; 256 threads give 16 columns their 16 lanes per root), else
+// a workgroup sized to the level's largest merge (levels of many merges are
+// throughput-bound).  LDS is sized to the largest merge too.
 static void launch_level_block(int smax, const MergeRec* mr, int M, const double* e, const Work& w, double* out,
-                               int gmax, void* stream) {
+                               int gmax, int save_roots, void* stream) {
     const unsigned long long* pm = (const unsigned long long*)w.pmax;
     const unsigned g = (unsigned)M;
-    if (smax > 128 && M <= kLevelBlockWideMerges)
-        TDE_LAUNCH_K(KIND_LEVEL, (k_level_block<2 * kFuseThreads, kFuseMax>), g, 2 * kFuseThreads, stream, mr, e, pm,
-                     w, out, gmax);
-    else if (smax > 256 || M <= kLevelBlockMaxMerges)
-        TDE_LAUNCH_K(KIND_LEVEL, (k_level_block<kFuseThreads, kFuseMax>), g, kFuseThreads, stream, mr, e, pm, w, out,
-                     gmax);
-    else if (smax > 128)
-        TDE_LAUNCH_K(KIND_LEVEL, (k_level_block<256, 256>), g, 256, stream, mr, e, pm, w, out, gmax);
-    else if (smax > 64)
-        TDE_LAUNCH_K(KIND_LEVEL, (k_level_block<128, 128>), g, 128, stream, mr, e, pm, w, out, gmax);
-    else
-        TDE_LAUNCH_K(KIND_LEVEL, (k_level_block<64, 64>), g, 64, stream, mr, e, pm, w, out, gmax);
+#define TDE_LEVEL(nt, cap) \
+    TDE_LAUNCH_K(KIND_LEVEL, (k_level_block<nt, cap>), g, nt, stream, mr, e, pm, w, out, gmax, save_roots)
+    if (M > kLevelBlockMaxMerges) {  // (merges of at most kLevelBlockSmallCols columns)
+        if (smax > 64) TDE_LEVEL(128, 128);
+        else TDE_LEVEL(64, 64);
+    } else if (smax <= 16) {
+        TDE_LEVEL(256, 64);
+    } else if (smax <= 64) {
+        TDE_LEVEL(512, 64);
+    } else if (smax <= 128) {
+        TDE_LEVEL(512, 128);
+    } else if (M <= kLevelBlockWideMerges) {
+        if (smax <= 256) TDE_LEVEL(1024, 256);
+        else TDE_LEVEL(1024, 512);
+    } else {
+        if (smax <= 256) TDE_LEVEL(512, 256);
+        else TDE_LEVEL(512, 512);
+    }
+#undef TDE_LEVEL
 }
 
 // no_rows: every merge of the level is a problem's top merge and no rows
@@ -3330,7 +3453,7 @@ int enqueue_solve(const Plan& p, const Work& w, const double* d, const double* e
                 TDE_LAUNCH_K(KIND_LEVEL, k_level_wave<4>, (unsigned)L.nwp, 64, stream, mr, p.d_blkm + L.wpstart, e,
                              (const unsigned long long*)w.pmax, wl, out, ck ? 1 : 0);
             else
-                launch_level_block(L.smax, mr, M, e, wl, out, fused_gmax(M, p.group_max), stream);
+                launch_level_block(L.smax, mr, M, e, wl, out, fused_gmax(M, p.group_max), ck ? 1 : 0, stream);
             continue;
         }
         launch_merge(KIND_MERGE, L, mr, blkm, e, wl, stream);
