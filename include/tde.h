@@ -176,14 +176,17 @@ int tde_eigvals_rows(const double* d, const double* e, const int64_t* offsets, i
  *                 column signed so that q_0k >= 0 (q_(n-1)k >= 0 when q_0k = 0),
  *                 the convention of tde_eigvals_rows; may be NULL when m = 0
  *   ws     ws_bytes >= tde_selrows_workspace_bytes(n, m, opts) (device): the
- *                 forward workspace, a checkpoint of the nodes' spectra and
- *                 boundary rows per tree level, and 5 n doubles + m ints
+ *                 workspace of the passes (below), a checkpoint of the nodes'
+ *                 spectra and boundary rows per tree level, the passes' rows
+ *                 and 2 n doubles + m ints.  The size for m <= 2 suffices for
+ *                 any m (m ints more): fewer rows then share a pass
  * Leaves are solved by QL (TDE_FLAG_LEAF_DC is ignored).  One forward solve
- * records every level's node spectra and boundary rows; then each pair of
- * distinct requested rows takes one more pass up the same tree, riding in
- * the two row channels the boundary rows use (deflation decisions and roots
- * are those of the first pass, bit for bit), so the cost is about
- * 1 + ceil(distinct rows / 2) forward solves.  Kernels are enqueued one by
+ * records every level's node spectra and boundary rows; then the distinct
+ * requested rows take further passes up the same tree, riding in the two row
+ * channels the boundary rows use (deflation decisions and roots are those of
+ * the first pass, bit for bit).  A pass solves up to eight copies of the
+ * problem side by side (at most 2^18 columns in all), two rows in each: 1 +
+ * ceil(distinct rows / 16) passes for n <= 32768.  Kernels are enqueued one by
  * one (no graph); the call waits for the stream once at the end.  Returns
  * TDE_OK or a negative code (TDE_EINVAL for a row outside [0, n)); device
  * status via tde_get_status(ws).  tde_selrows_workspace_bytes returns 0 on a

@@ -372,37 +372,51 @@ int backward(const double* d, const double* e, const std::vector<long long>& off
 }
 
 // Requested rows (Algorithm 1 with an arbitrary row list sigma): the
-// workspace beyond the forward's holds a forward checkpoint, the current
-// nodes' vectors of the two rows a pass carries, the unsigned top rows 0 and
-// n-1, a discarded eigenvalue output and the first-occurrence map.
+// workspace of the passes (each solves `copies` copies of the problem side by
+// side, two rows in each) starts with the forward's; beyond it lie a forward
+// checkpoint, the rows the passes carry, the unsigned top rows 0 and n-1, the
+// copies' matrix, their row numbers and the requests' distinct rows.
 struct SelLayout {
-    size_t fw, total;
     Ckpt ck;
-    double *xa, *xb, *q0, *q1, *xout;
-    int* first;
+    double *xa, *xb, *q0, *q1, *dr, *er;
+    long long* rows;
+    int* slot;
 };
 
-size_t selrows_layout(long long n, long long m, int levels, char* base, SelLayout* L) {
+size_t selrows_layout(long long n, long long m, int levels, int copies, char* base, SelLayout* L) {
     SelLayout t{};
-    t.fw = workspace_layout(n, 1, n, nullptr, nullptr);
-    size_t off = t.fw;
+    const long long c = copies;
+    size_t off = workspace_layout(c * n, c, c * n, nullptr, nullptr);
     auto take = [&](size_t bytes) -> char* {
         char* p = base ? base + off : nullptr;
         off += (bytes + 255) & ~(size_t)255;
         return p;
     };
-    const long long nn = n > 0 ? n : 1;
+    const size_t nn = (size_t)(n > 0 ? n : 1);
     char* ckb = take(ckpt_layout(n, levels, nullptr, nullptr));
     ckpt_layout(n, levels, ckb, &t.ck);
-    t.xa = (double*)take(8 * nn);
-    t.xb = (double*)take(8 * nn);
+    t.xa = (double*)take(8 * nn * (size_t)c);
+    t.xb = (double*)take(8 * nn * (size_t)c);
     t.q0 = (double*)take(8 * nn);
     t.q1 = (double*)take(8 * nn);
-    t.xout = (double*)take(8 * nn);
-    t.first = (int*)take(4 * (m > 0 ? m : 1));
-    t.total = off;
+    t.rows = (long long*)take(16 * (size_t)c);
+    if (copies > 1) {  // one copy reads the caller's matrix
+        t.dr = (double*)take(8 * nn * (size_t)c);
+        t.er = (double*)take(8 * nn * (size_t)c);
+    }
+    t.slot = (int*)take(4 * (size_t)(m > 0 ? m : 1));
     if (L) *L = t;
     return off;
+}
+
+// Copies per pass for m requests: enough for every row in one pass, while the
+// passes of a small matrix are chains of latencies that cost the same for
+// eight copies as for one (n = 3001, 12 rows: six passes of 0.6 ms each, or one
+// of 0.7 ms), and the workspace stays near 300 bytes times 2^18 columns.
+int selrows_copies(long long n, long long m) {
+    long long c = (m + 1) / 2;
+    c = std::min(c, std::min(8LL, (1LL << 18) / std::max(n, 1LL)));
+    return (int)std::max(c, 1LL);
 }
 
 int selrows(const double* d, const double* e, long long n, const int64_t* rows, long long m, double* lambda,
@@ -420,23 +434,27 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
     if (opts) o = *opts;
     o.flags &= ~TDE_FLAG_LEAF_DC;
     std::lock_guard<std::recursive_mutex> lk(g_mu);
-    const std::vector<long long> offs{0, n};
     Plan* plan = nullptr;
-    int rc = get_plan(&o, offs, &plan);
+    int rc = get_plan(&o, {0, n}, &plan);
     if (rc != TDE_OK) return rc;
-    SelLayout sl{};
-    const int H = tree_levels(leaf, offs);
-    if ((int)plan->levels.size() > H || ws_bytes < selrows_layout(n, m, H, nullptr, nullptr)) return TDE_EINVAL;
-    selrows_layout(n, m, H, (char*)ws, &sl);
-    // distinct rows, ascending, and the first request of each
-    std::vector<int> first((size_t)(m > 0 ? m : 1));
-    std::map<long long, int> slot;
-    for (long long i = 0; i < m; ++i) {
-        auto it = slot.find(rows[i]);
-        if (it == slot.end()) it = slot.emplace(rows[i], (int)i).first;
-        first[(size_t)i] = it->second;
+    const int H = tree_levels(leaf, {0, n});
+    if ((int)plan->levels.size() > H) return TDE_EINVAL;
+    // distinct rows, ascending, and the one each request wants
+    std::map<long long, int> distinct;
+    for (long long i = 0; i < m; ++i) distinct.emplace(rows[i], 0);
+    std::vector<long long> uniq;
+    for (auto& u : distinct) {
+        u.second = (int)uniq.size();
+        uniq.push_back(u.first);
     }
-    std::vector<std::pair<long long, int>> uniq(slot.begin(), slot.end());
+    std::vector<int> slot((size_t)m);
+    for (long long i = 0; i < m; ++i) slot[(size_t)i] = distinct[rows[i]];
+    // as many copies per pass as the rows need and the workspace holds
+    int copies = selrows_copies(n, (long long)uniq.size());
+    while (copies > 1 && ws_bytes < selrows_layout(n, m, H, copies, nullptr, nullptr)) --copies;
+    if (ws_bytes < selrows_layout(n, m, H, copies, nullptr, nullptr)) return TDE_EINVAL;
+    SelLayout sl{};
+    selrows_layout(n, m, H, copies, (char*)ws, &sl);
     Work w{};
     workspace_layout(n, 1, n, (char*)ws, &w);
     w.sec_cap = cap;
@@ -446,33 +464,46 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
     w.qfirst = sl.q0;
     w.qlast = sl.q1;
     if (enqueue_solve(*plan, w, d, e, lambda, stream, &sl.ck) != 0) return TDE_EDEVICE;
-    // one pass per two distinct rows
-    for (size_t u = 0; u < uniq.size(); u += 2) {
-        Work wx = w;
-        wx.qfirst = wx.qlast = nullptr;
-        wx.rows_raw = 0;
+    if (m == 0) return TDE_OK;
+    const hipStream_t s = (hipStream_t)stream;
+    if (hipMemcpyAsync(sl.slot, slot.data(), sizeof(int) * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess)
+        return TDE_EDEVICE;
+    std::vector<std::vector<long long>> pass_rows;  // outlive their copies (the stream is waited for below)
+    for (size_t u = 0; u < uniq.size(); u += 2 * (size_t)copies) {
+        const int c = (int)std::min((uniq.size() - u + 1) / 2, (size_t)copies);
+        // the pass's plan: c copies of the problem
+        Plan* px = nullptr;
+        std::vector<long long> offs;
+        for (int p = 0; p <= c; ++p) offs.push_back(p * n);
+        rc = get_plan(&o, offs, &px);
+        if (rc != TDE_OK) return rc;
+        if ((int)px->levels.size() > H) return TDE_EINVAL;
+        std::vector<long long> r((size_t)(2 * c), -1);
+        for (size_t k = 0; k < r.size() && u + k < uniq.size(); ++k) r[k] = uniq[u + k];
+        pass_rows.push_back(std::move(r));
+        if (hipMemcpyAsync(sl.rows, pass_rows.back().data(), 8 * 2 * (size_t)c, hipMemcpyHostToDevice, s) != hipSuccess)
+            return TDE_EDEVICE;
+        const double *dx = d, *ex = e;
+        if (c > 1) {
+            if (enqueue_selrows_copies(d, e, n, c, sl.dr, sl.er, stream) != 0) return TDE_EDEVICE;
+            dx = sl.dr;
+            ex = sl.er;
+        }
+        Work wx{};
+        workspace_layout(c * n, c, c * n, (char*)ws, &wx);
+        wx.sec_cap = cap;
+        wx.rows_out = 1;
         wx.xmode = 1;
+        wx.xn = n;
+        wx.xrows = sl.rows;
         wx.xa = sl.xa;
         wx.xb = sl.xb;
-        wx.xa_row = uniq[u].first;
-        wx.xq_a = Q + (size_t)uniq[u].second * (size_t)n;
-        if (u + 1 < uniq.size()) {
-            wx.xb_row = uniq[u + 1].first;
-            wx.xq_b = Q + (size_t)uniq[u + 1].second * (size_t)n;
-        } else {
-            wx.xb_row = -1;
-            wx.xq_b = nullptr;
-        }
-        if (enqueue_solve(*plan, wx, d, e, sl.xout, stream, nullptr, &sl.ck) != 0) return TDE_EDEVICE;
-    }
-    if (m > 0) {
-        if (hipMemcpyAsync(sl.first, first.data(), sizeof(int) * (size_t)m, hipMemcpyHostToDevice,
-                           (hipStream_t)stream) != hipSuccess)
+        if (enqueue_solve(*px, wx, dx, ex, lambda, stream, nullptr, &sl.ck) != 0) return TDE_EDEVICE;
+        if (enqueue_selrows_out(Q, m, n, sl.slot, (int)u, c, sl.xa, sl.xb, sl.q0, sl.q1, stream) != 0)
             return TDE_EDEVICE;
-        if (enqueue_selrows_fix(Q, m, n, sl.first, sl.q0, sl.q1, stream) != 0) return TDE_EDEVICE;
-        // the host map must outlive the copy: wait for it (pageable memory)
-        if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return TDE_EDEVICE;
     }
+    // the host tables must outlive their copies (pageable memory)
+    if (hipStreamSynchronize(s) != hipSuccess) return TDE_EDEVICE;
     return TDE_OK;
 }
 
@@ -658,7 +689,7 @@ size_t tde_selrows_workspace_bytes(int64_t n, int64_t m, const tde_opts* opts) {
     int leaf, cols;
     if (n < 0 || m < 0 || tde::resolve_opts(opts, &leaf, &cols) != TDE_OK) return 0;
     const std::vector<long long> offs{0, (long long)n};
-    return tde::selrows_layout(n, m, tde::tree_levels(leaf, offs), nullptr, nullptr);
+    return tde::selrows_layout(n, m, tde::tree_levels(leaf, offs), tde::selrows_copies(n, m), nullptr, nullptr);
 }
 
 int tde_eigvals_selrows(const double* d, const double* e, int64_t n, const int64_t* rows, int64_t m,

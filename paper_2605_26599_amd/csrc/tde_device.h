@@ -703,13 +703,24 @@ TDE_DEV void root_rows(int K, const double* __restrict__ D, const double* __rest
 // i = t - mr[m].pk; callers find m (find_merge / find_merge_in).
 // ---------------------------------------------------------------------------
 
+// Where a merge's children lie in the node arrays lam, blo, bhi: the copies
+// of a requested-rows pass share those of the one problem.
+TDE_DEV long long node_off(const MergeRec& R, const Work& w) {
+    return w.xmode ? R.off - (long long)R.prob * w.xn : R.off;
+}
+// Requested row of a problem's channel (0 or 1) as a packed position, or -1.
+TDE_DEV long long xrow(const Work& w, int prob, int channel) {
+    const long long r = w.xrows[2 * prob + channel];
+    return r < 0 ? -1 : r + (long long)prob * w.xn;
+}
+
 // (a3/a4) z~, outer rows and merged sorted order of one child column.
 // Left column i: position i + #{right values < x}; right column j:
 // j + #{left values <= x} (ties go left first).  Returns the packed position.
 // The deflation tolerance of merge R from its children's spectra (the same
 // value as merge_tol on the merged poles: the ends of both sorted children).
 TDE_DEV double merge_tol_children(const MergeRec& R, const Work& w) {
-    const double* lamL = w.lam + R.off;
+    const double* lamL = w.lam + node_off(R, w);
     const double* lamR = lamL + R.nL;
     const double dmax = fmax(fmax(fabs(lamL[0]), fabs(lamL[R.nL - 1])), fmax(fabs(lamR[0]), fabs(lamR[R.nR - 1])));
     return 8.0 * DBL_EPSILON * fmax(dmax, 1.0);
@@ -721,22 +732,24 @@ TDE_DEV double merge_tol_children(const MergeRec& R, const Work& w) {
 TDE_DEV int merge_emit(const MergeRec& R, int c, double x, double rho, double sgn, double tol, const Work& w,
                        long long P) {
     const double rs2 = 0.70710678118654752440;  // 1/sqrt(2)
+    const long long no = node_off(R, w) + c;
     double z, rl, rh;
     if (c < R.nL) {
-        z = w.bhi[R.off + c] * rs2;
-        rl = w.blo[R.off + c];
+        z = w.bhi[no] * rs2;
+        rl = w.blo[no];
         rh = 0.0;
     } else {
-        z = sgn * w.blo[R.off + c] * rs2;
+        z = sgn * w.blo[no] * rs2;
         rl = 0.0;
-        rh = w.bhi[R.off + c];
+        rh = w.bhi[no];
     }
     if (w.xmode) {
         // requested rows: a row reaches this merge from the child that holds it
         const bool cl = c < R.nL;
         const long long mid = R.off + R.nL, end = mid + R.nR;
-        rl = (w.xa_row >= R.off && w.xa_row < end && (w.xa_row < mid) == cl) ? w.xa[R.off + c] : 0.0;
-        rh = (w.xb_row >= R.off && w.xb_row < end && (w.xb_row < mid) == cl) ? w.xb[R.off + c] : 0.0;
+        const long long ra = xrow(w, R.prob, 0), rb = xrow(w, R.prob, 1);
+        rl = (ra >= R.off && ra < end && (ra < mid) == cl) ? w.xa[R.off + c] : 0.0;
+        rh = (rb >= R.off && rb < end && (rb < mid) == cl) ? w.xb[R.off + c] : 0.0;
     }
     w.D[P] = x;
     w.Z[P] = z;
@@ -795,7 +808,7 @@ TDE_DEV long long body_merge(long long t, int m, const MergeRec* __restrict__ mr
     const int i = (int)(t - R.pk);
     double sgn;
     const double rho = merge_rho(R, e, pmax, &sgn);
-    const double* lamL = w.lam + R.off;
+    const double* lamL = w.lam + node_off(R, w);
     const double* lamR = lamL + R.nL;
     const double tol = merge_tol_children(R, w);
     int pos;
@@ -1092,15 +1105,9 @@ TDE_DEV void body_assemble(long long t, int m, const MergeRec* __restrict__ mr,
     }
     const long long P = R.off + pos;
     if (w.xmode) {
-        const bool ha = w.xa_row >= R.off && w.xa_row < R.off + s;
-        const bool hb = w.xb_row >= R.off && w.xb_row < R.off + s;
-        if (root) {
-            if (ha && w.xq_a) w.xq_a[P] = bl;
-            if (hb && w.xq_b) w.xq_b[P] = bh;
-        } else {
-            if (ha) w.xa[P] = bl;
-            if (hb) w.xb[P] = bh;
-        }
+        const long long ra = xrow(w, R.prob, 0), rb = xrow(w, R.prob, 1);
+        if (ra >= R.off && ra < R.off + s) w.xa[P] = bl;
+        if (rb >= R.off && rb < R.off + s) w.xb[P] = bh;
         return;
     }
     if (root) {
@@ -1130,16 +1137,14 @@ TDE_DEV int body_leaf(const LeafRec& L, const double* __restrict__ d, const doub
     }
     // tracked rows: 0 and l-1, or in a requested-rows pass the requested rows
     // the leaf holds
-    const bool ha = w.xmode && w.xa_row >= L.off && w.xa_row < L.off + nl;
-    const bool hb = w.xmode && w.xb_row >= L.off && w.xb_row < L.off + nl;
-    int status = leaf_ql(nl, sd, se, s0, s1, st, nrot, ha ? (int)(w.xa_row - L.off) : 0,
-                         hb ? (int)(w.xb_row - L.off) : nl - 1);
+    const long long ra = w.xmode ? xrow(w, L.prob, 0) : -1, rb = w.xmode ? xrow(w, L.prob, 1) : -1;
+    const bool ha = ra >= L.off && ra < L.off + nl;
+    const bool hb = rb >= L.off && rb < L.off + nl;
+    int status = leaf_ql(nl, sd, se, s0, s1, st, nrot, ha ? (int)(ra - L.off) : 0, hb ? (int)(rb - L.off) : nl - 1);
     if (w.xmode) {
-        double* da = (L.flags & LF_WHOLE) ? w.xq_a : w.xa;
-        double* db = (L.flags & LF_WHOLE) ? w.xq_b : w.xb;
         for (int i = 0; i < nl; ++i) {
-            if (ha && da) da[L.off + i] = s0[i * st];
-            if (hb && db) db[L.off + i] = s1[i * st];
+            if (ha) w.xa[L.off + i] = s0[i * st];
+            if (hb) w.xb[L.off + i] = s1[i * st];
         }
         return status;
     }

@@ -160,18 +160,19 @@ struct Work {
     int rows_out;              // 1: the top merges also propagate rows (qfirst / qlast requested)
     int sec_cap;               // secular iterations allowed per root before ST_SEC_NOCONV (kSecMaxIter)
     int rows_raw;              // rows mode: store the top rows as computed (no sign normalisation)
-    // Requested-rows pass (xmode = 1): the two row channels carry rows xa_row and
-    // xb_row of every node that contains them (global indices, -1 = none) instead
-    // of the parent's first and last rows; z still comes from the node boundary
-    // rows (lam, blo, bhi then point at a forward checkpoint's level slot, read
-    // only).  xa / xb hold those rows of the current nodes (global positions, in
-    // place across levels); the top merge writes them to xq_a / xq_b (length n).
+    // Requested-rows pass (xmode = 1), several copies of one problem side by
+    // side (problem p of the pass = copy p, xn columns each): copy p's two row
+    // channels carry rows xrows[2p] and xrows[2p + 1] (device; -1 = none) of
+    // every node that contains them instead of the parent's first and last
+    // rows; z still comes from the node boundary rows (lam, blo, bhi then point
+    // at a forward checkpoint's level slot of the one problem, read only).
+    // xa / xb hold those rows of the current nodes (packed positions over the
+    // copies, in place across levels) and at the end of the top nodes.
     int xmode;
-    long long xa_row, xb_row;
+    long long xn;
+    const long long* xrows;
     double* xa;
     double* xb;
-    double* xq_a;
-    double* xq_b;
 };
 
 // Forward checkpoint for the reverse pass: per level h (slot stride n), the

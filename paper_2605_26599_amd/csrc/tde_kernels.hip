@@ -634,7 +634,7 @@ __global__ __launch_bounds__(kWG) void k_merge_path(const MergeRec* __restrict__
         const long long gb = (p1 < R.pk + s) ? p1 : R.pk + s;
         if (ga >= gb) continue;  // block-uniform
         const int a = (int)(ga - R.pk), bnd = (int)(gb - R.pk);
-        const double* lamL = w.lam + R.off;
+        const double* lamL = w.lam + node_off(R, w);
         const double* lamR = lamL + R.nL;
         // co-ranks of a (first half) and bnd (second half)
         const int pe = half ? bnd : a;
@@ -2473,17 +2473,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const bool col = t < s;
     double x = 0.0, lo = 0.0, hi = 0.0;
     if (col) {
-        x = w.lam[R.off + t];
-        lo = w.blo[R.off + t];
-        hi = w.bhi[R.off + t];
+        const long long no = node_off(R, w) + t;
+        x = w.lam[no];
+        lo = w.blo[no];
+        hi = w.bhi[no];
     }
     double xl = 0.0, xh = 0.0;
     if (w.xmode && col) {
         // requested rows: a row reaches this merge from the child that holds it
         const bool left = t < R.nL;
         const long long mid = R.off + R.nL, end = mid + R.nR;
-        if (w.xa_row >= R.off && w.xa_row < end && (w.xa_row < mid) == left) xl = w.xa[R.off + t];
-        if (w.xb_row >= R.off && w.xb_row < end && (w.xb_row < mid) == left) xh = w.xb[R.off + t];
+        const long long ra = xrow(w, R.prob, 0), rb = xrow(w, R.prob, 1);
+        if (ra >= R.off && ra < end && (ra < mid) == left) xl = w.xa[R.off + t];
+        if (rb >= R.off && rb < end && (rb < mid) == left) xh = w.xb[R.off + t];
     }
     double sgn;
     const double rho = merge_rho(R, e, pmax, &sgn);
@@ -2566,15 +2568,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const long long P = R.off + pos;
         const bool top = (R.flags & MF_ROOT) != 0;
         if (w.xmode) {
-            const bool ha = w.xa_row >= R.off && w.xa_row < R.off + s;
-            const bool hb = w.xb_row >= R.off && w.xb_row < R.off + s;
-            if (top) {
-                if (ha && w.xq_a) w.xq_a[P] = bl;
-                if (hb && w.xq_b) w.xq_b[P] = bh;
-            } else {
-                if (ha) w.xa[P] = bl;
-                if (hb) w.xb[P] = bh;
-            }
+            const long long ra = xrow(w, R.prob, 0), rb = xrow(w, R.prob, 1);
+            if (ra >= R.off && ra < R.off + s) w.xa[P] = bl;
+            if (rb >= R.off && rb < R.off + s) w.xb[P] = bh;
         } else if (top) {
             out[P] = val * scale_of(pmax[R.prob]);
             if (w.rows_out) store_rows(w, P, bl, bh);
@@ -3048,21 +3044,38 @@ __global__ __launch_bounds__(kWG) void k_bwd_edges(const long long* __restrict__
     if (b < B && offs[b + 1] > offs[b]) ge[offs[b + 1] - 1] = 0.0;
 }
 
-// Requested rows: sign every eigenvector column like the boundary rows (the
-// first entry >= 0, the last when the first is 0; q0 / q1 are the unsigned top
-// rows of the same solve) and copy repeated requests from their first
-// occurrence.  One thread per column; Q is [m][n], row i at Q + i n.
-__global__ __launch_bounds__(kWG) void k_selrows_fix(double* __restrict__ Q, long long m, long long n,
-                                                     const int* __restrict__ first, const double* __restrict__ q0,
-                                                     const double* __restrict__ q1) {
+// Requested rows: the rows of one pass to their places in Q [m][n], every
+// eigenvector column signed like the boundary rows (the first entry >= 0, the
+// last when the first is 0; q0 / q1 are the unsigned top rows of the same
+// solve).  Request i wants distinct row slot[i]; the pass holds the slots
+// [u0, u0 + 2 copies), slot u0 + 2p + c in channel c of copy p.  One thread
+// per column.
+__global__ __launch_bounds__(kWG) void k_selrows_out(double* __restrict__ Q, long long m, long long n,
+                                                     const int* __restrict__ slot, int u0, int copies,
+                                                     const double* __restrict__ xa, const double* __restrict__ xb,
+                                                     const double* __restrict__ q0, const double* __restrict__ q1) {
     const long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (k >= n) return;
     const double a = q0[k], b = q1[k];
     const double sg = (a < 0.0 || (a == 0.0 && b < 0.0)) ? -1.0 : 1.0;
-    for (long long i = 0; i < m; ++i)
-        if (first[i] == i) Q[i * n + k] *= sg;
-    for (long long i = 0; i < m; ++i)
-        if (first[i] != i) Q[i * n + k] = Q[(long long)first[i] * n + k];
+    for (long long i = 0; i < m; ++i) {
+        const int u = slot[i] - u0;
+        if (u < 0 || u >= 2 * copies) continue;
+        Q[i * n + k] = ((u & 1) ? xb : xa)[(long long)(u >> 1) * n + k] * sg;
+    }
+}
+
+// The matrix of a requested-rows pass: `copies` times (d, e), batched layout.
+__global__ __launch_bounds__(kWG) void k_selrows_copies(const double* __restrict__ d, const double* __restrict__ e,
+                                                        long long n, int copies, double* __restrict__ dr,
+                                                        double* __restrict__ er) {
+    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const double x = d[i], y = (i + 1 < n) ? e[i] : 0.0;
+    for (int p = 0; p < copies; ++p) {
+        dr[p * n + i] = x;
+        er[p * n + i] = y;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -3628,10 +3641,17 @@ __global__ __launch_bounds__(kWG) void k_merge_runs(const MergeRec* __restrict__
     dst[R.off + pos] = x;
 }
 
-int enqueue_selrows_fix(double* Q, long long m, long long n, const int* first, const double* q0,
-                        const double* q1, void* stream) {
+int enqueue_selrows_out(double* Q, long long m, long long n, const int* slot, int u0, int copies, const double* xa,
+                        const double* xb, const double* q0, const double* q1, void* stream) {
     if (m <= 0 || n <= 0) return 0;
-    TDE_LAUNCH_K(KIND_ASSEMBLE, k_selrows_fix, nblk(n, kWG), kWG, stream, Q, m, n, first, q0, q1);
+    TDE_LAUNCH_K(KIND_ASSEMBLE, k_selrows_out, nblk(n, kWG), kWG, stream, Q, m, n, slot, u0, copies, xa, xb, q0, q1);
+    return (int)hipGetLastError();
+}
+
+int enqueue_selrows_copies(const double* d, const double* e, long long n, int copies, double* dr, double* er,
+                           void* stream) {
+    if (n <= 0) return 0;
+    TDE_LAUNCH_K(KIND_SETUP, k_selrows_copies, nblk(n, kWG), kWG, stream, d, e, n, copies, dr, er);
     return (int)hipGetLastError();
 }
 

@@ -88,11 +88,13 @@ int enqueue_solve(const Plan& p, const Work& w, const double* d, const double* e
 // spectra and boundary rows from the checkpoint xsrc of a forward solve of the
 // same inputs and plan instead of the workspace.
 
-// Requested rows: sign the columns of Q [m][n] by the unsigned top rows q0, q1
-// (first entry >= 0) and copy repeated rows from their first occurrence
-// first[i] (device).
-int enqueue_selrows_fix(double* Q, long long m, long long n, const int* first, const double* q0,
-                        const double* q1, void* stream);
+// Requested rows: `copies` times (d, e) in the batched layout, and one pass's
+// rows to Q [m][n], signed by the unsigned top rows q0, q1 (first entry >= 0);
+// slot[i] (device): the distinct row that request i wants.
+int enqueue_selrows_copies(const double* d, const double* e, long long n, int copies, double* dr, double* er,
+                           void* stream);
+int enqueue_selrows_out(double* Q, long long m, long long n, const int* slot, int u0, int copies, const double* xa,
+                        const double* xb, const double* q0, const double* q1, void* stream);
 
 // Driver pre-pass: negligible-coupling flags (flags[i] = 1: a block starts at
 // column i), and one pass of pairwise merges of ascending runs (src -> dst).

@@ -156,3 +156,32 @@ def test_selrows_arguments(tde):
     lam, Q = _sel(tde, d, e, [])
     assert Q.shape == (0, 100)
     assert np.abs(lam - oracle.eigvals(d, e)).max() <= 2e-11 * tdgen.tnorm1(d, e)
+
+
+@pytest.mark.parametrize("n,m", [(1, 3), (2, 4), (40, 17), (513, 16), (513, 33), (2500, 5)])
+def test_selrows_shared_passes(tde, n, m):
+    """Rows that share a pass (up to sixteen, two in each copy of the problem)
+    equal, bit for bit, the same rows taken two at a time, which a workspace
+    of that size makes of the same call."""
+    import ctypes
+
+    import torch
+
+    g = np.random.default_rng(n + m)
+    d, e = tdgen.tridiag("uniform", n, cfg=tdgen.CFG_TEST)
+    rows = [int(r) for r in g.integers(0, n, m)]
+    _step(f"selrows shared passes n={n} m={m}")
+    lam, Q = _sel(tde, d, e, rows)
+    L = tde.lib()
+    nb = L.tde_selrows_workspace_bytes(n, 1, None) + 4 * m
+    dv, ev = _t(d), _t(e if len(e) else np.zeros(1))
+    lam2 = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    Q2 = torch.empty((m, n), dtype=torch.float64, device="cuda:0")
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda:0")
+    arr = (ctypes.c_int64 * m)(*rows)
+    stream = torch.cuda.current_stream().cuda_stream
+    args = (dv.data_ptr(), ev.data_ptr(), n, arr, m, lam2.data_ptr(), Q2.data_ptr(), ws.data_ptr())
+    assert L.tde_eigvals_selrows(*args, nb, stream, None) == tde.TDE_OK
+    assert L.tde_get_status(ws.data_ptr(), stream) == tde.TDE_OK
+    assert np.array_equal(lam, lam2.cpu().numpy()) and np.array_equal(Q, Q2.cpu().numpy())
+    assert L.tde_eigvals_selrows(*args, nb - 4 * m - 256, stream, None) == tde.TDE_EINVAL
