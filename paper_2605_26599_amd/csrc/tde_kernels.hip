@@ -1876,9 +1876,12 @@ struct Canon {
 };
 
 // Runs body(q, j) for every term j < K of this lane's partials q, in
-// increasing j per partial (whole chunks of 16 first, then the tail).
-template <int G, class Body>
-__device__ __forceinline__ void canon_for(int K, int sub, Body body) {
+// increasing j per partial: whole chunks of 16 first, chunk_done() after each,
+// then the tail.  (Running the tail's missing terms too, as terms of no weight,
+// shortens a lone merge's chain but costs issue slots: a batch's whole-merge
+// workgroups 1.36 -> 1.43 ms.)
+template <int G, class Body, class Done>
+__device__ __forceinline__ void canon_for(int K, int sub, Body body, Done chunk_done) {
     constexpr int M = Canon<G>::M;
     int off[M];
 #pragma unroll
@@ -1887,25 +1890,51 @@ __device__ __forceinline__ void canon_for(int K, int sub, Body body) {
     _Pragma("unroll 2") for (; c + 16 <= K; c += 16) {
 #pragma unroll
         for (int q = 0; q < M; ++q) body(q, c + off[q]);
+        chunk_done();
     }
 #pragma unroll
     for (int q = 0; q < M; ++q)
         if (c + off[q] < K) body(q, c + off[q]);
 }
+template <int G, class Body>
+__device__ __forceinline__ void canon_for(int K, int sub, Body body) {
+    canon_for<G>(K, sub, body, [] {});
+}
 
-// The same canonical value from one lane: partial(s) accumulates terms
-// j = s, s + 16, ... in increasing j; the partials meet in the tree above:
-// B_q = (P_q + P_15-q) + (P_7-q + P_8+q) for q < 4, then (B_0 + B_2) +
-// (B_1 + B_3).  The B_q are formed one per loop trip (in the order 0, 2, 1,
-// 3) so that only four partials are live at a time.  Addition and
+// The same canonical value from one lane: partial s accumulates terms j = s,
+// s + 16, ... in increasing j (term(a, j); chunk_done(a) after every whole
+// chunk, finish(a) at the end); the partials meet in the tree above: B_q = (P_q +
+// P_15-q) + (P_7-q + P_8+q) for q < 4, then (B_0 + B_2) + (B_1 + B_3).  The B_q
+// are formed one per loop trip (in the order 0, 2, 1, 3), their four partials
+// side by side, so four independent terms are in flight.  Addition and
 // multiplication commute exactly, so the order inside each pair is free.
-template <class Part, class Op>
-__device__ __forceinline__ auto canon1(Part part, Op op) {
-    decltype(part(0)) c0{}, c1{};
+template <class Acc, class Term, class Done, class Finish, class Op>
+__device__ __forceinline__ auto canon1(int K, Acc zero, Term term, Done chunk_done, Finish finish, Op op) {
+    Acc c0{}, c1{};
 #pragma unroll 1
     for (int t = 0; t < 4; ++t) {
         const int q = (t == 0) ? 0 : ((t == 1) ? 2 : ((t == 2) ? 1 : 3));
-        const auto b = op(op(part(q), part(15 - q)), op(part(7 - q), part(8 + q)));
+        Acc a0 = zero, a1 = zero, a2 = zero, a3 = zero;
+        int c = 0;
+        for (; c + 16 <= K; c += 16) {
+            term(a0, c + q);
+            term(a1, c + 15 - q);
+            term(a2, c + 7 - q);
+            term(a3, c + 8 + q);
+            chunk_done(a0);
+            chunk_done(a1);
+            chunk_done(a2);
+            chunk_done(a3);
+        }
+        if (c + q < K) term(a0, c + q);
+        if (c + 7 - q < K) term(a2, c + 7 - q);
+        if (c + 8 + q < K) term(a3, c + 8 + q);
+        if (c + 15 - q < K) term(a1, c + 15 - q);
+        finish(a0);
+        finish(a1);
+        finish(a2);
+        finish(a3);
+        const Acc b = op(op(a0, a1), op(a2, a3));
         if (t == 0) c0 = b;
         else if (t == 1) c0 = op(c0, b);
         else if (t == 2) c1 = b;
@@ -1919,7 +1948,6 @@ struct Sums3 {
 };
 __device__ __forceinline__ Sums3 add3(const Sums3& x, const Sums3& y) { return Sums3{x.a + y.a, x.b + y.b, x.c + y.c}; }
 __device__ __forceinline__ double add1(double x, double y) { return x + y; }
-__device__ __forceinline__ double mul1(double x, double y) { return x * y; }
 
 // sec_sweep with canonical partial sums (same per-term arithmetic): a group of
 // G = 4, 8 or 16 lanes, or one lane (G = 1).
@@ -1927,25 +1955,20 @@ template <int G>
 __device__ __forceinline__ void sec_sweep_c(int K, const double* __restrict__ D, const double* __restrict__ W,
                                             double Do, double tau, int L1, int R0, int sub, SecSums* s) {
     const unsigned exw = (unsigned)(R0 - L1);
+    auto term = [&](SecSums& a, int j) {
+        sec_term(D[j], weight_unless((unsigned)(j - L1) < exw, W[j]), Do, tau, &a);
+    };
     if constexpr (G == 1) {
-        *s = canon1(
-            [&](int q) {
-                SecSums a{0.0, 0.0, 0.0, 0.0};
-                for (int j = q; j < K; j += 16)
-                    sec_term(D[j], weight_unless((unsigned)(j - L1) < exw, W[j]), Do, tau, &a);
-                return a;
-            },
-            [](const SecSums& x, const SecSums& y) {
-                return SecSums{x.t + y.t, x.dt + y.dt, x.at + y.at, x.adt + y.adt};
-            });
+        *s = canon1(K, SecSums{0.0, 0.0, 0.0, 0.0}, term, [](SecSums&) {}, [](SecSums&) {},
+                    [](const SecSums& x, const SecSums& y) {
+                        return SecSums{x.t + y.t, x.dt + y.dt, x.at + y.at, x.adt + y.adt};
+                    });
     } else {
         constexpr int M = Canon<G>::M;
         SecSums a[M];
 #pragma unroll
         for (int q = 0; q < M; ++q) a[q] = SecSums{0.0, 0.0, 0.0, 0.0};
-        canon_for<G>(K, sub, [&](int q, int j) {
-            sec_term(D[j], weight_unless((unsigned)(j - L1) < exw, W[j]), Do, tau, &a[q]);
-        });
+        canon_for<G>(K, sub, [&](int q, int j) { term(a[q], j); });
         auto total = [&](auto field) {
             double p[M];
 #pragma unroll
@@ -1962,24 +1985,18 @@ __device__ __forceinline__ void sec_sweep_c(int K, const double* __restrict__ D,
 // Canonical sum of W[0..K).
 template <int G>
 __device__ __forceinline__ double canon_wsum(int K, const double* __restrict__ W, int sub) {
+    auto term = [&](double& a, int j) { a += W[j]; };
     if constexpr (G == 1) {
-        return canon1(
-            [&](int q) {
-                double a = 0.0;
-                for (int j = q; j < K; j += 16) a += W[j];
-                return a;
-            },
-            add1);
+        return canon1(K, 0.0, term, [](double&) {}, [](double&) {}, add1);
     } else {
         constexpr int M = Canon<G>::M;
         double zz[M];
 #pragma unroll
         for (int q = 0; q < M; ++q) zz[q] = 0.0;
-        canon_for<G>(K, sub, [&](int q, int j) { zz[q] += W[j]; });
+        canon_for<G>(K, sub, [&](int q, int j) { term(zz[q], j); });
         return Canon<G>::sum(zz);
     }
 }
-
 
 // secular_root with canonical sweeps (same iteration and stopping rules).
 template <int G>
@@ -2021,67 +2038,57 @@ __device__ __forceinline__ int secular_root_c(int k, int K, const double* __rest
 
 // lowner_z with canonical partial products: each partial multiplies its
 // factors 8 at a time (one division per 8 of its factors), as lowner_z does.
+struct Ratio {
+    double prod, pn, pd;
+    int cnt;
+};
 template <int G>
 __device__ __forceinline__ double lowner_z_c(int i, int K, const double* __restrict__ D,
                                              const double* __restrict__ Z, const int* __restrict__ org,
                                              const double* __restrict__ tau, double rho, int sub) {
     const double di = D[i];
+    auto term = [&](Ratio& a, int k) {
+        // the pole paired with root k (the last root stands alone)
+        const double dk = D[min(k < i ? k : k + 1, K - 1)] - di;
+        a.pn *= (D[org[k]] - di) + tau[k];
+        a.pd *= (k >= i && k >= K - 1) ? 1.0 : dk;
+    };
+    auto fold = [](Ratio& a) {
+        a.prod *= a.pn / a.pd;
+        a.pn = 1.0;
+        a.pd = 1.0;
+    };
+    auto chunk = [&](Ratio& a) {
+        if (++a.cnt == 8) {
+            fold(a);
+            a.cnt = 0;
+        }
+    };
+    const Ratio one{1.0, 1.0, 1.0, 0};
+    double z2;
     if constexpr (G == 1) {
-        const double z2 = canon1(
-                              [&](int q) {
-                                  double prod = 1.0, pn = 1.0, pd = 1.0;
-                                  int cnt = 0;
-                                  for (int k = q; k < K; k += 16) {
-                                      const double num = (D[org[k]] - di) + tau[k];
-                                      double den;
-                                      if (k < i) den = D[k] - di;
-                                      else if (k < K - 1) den = D[k + 1] - di;
-                                      else den = 1.0;
-                                      pn *= num;
-                                      pd *= den;
-                                      if (++cnt == 8) {
-                                          prod *= pn / pd;
-                                          pn = 1.0;
-                                          pd = 1.0;
-                                          cnt = 0;
-                                      }
-                                  }
-                                  return prod * (pn / pd);
-                              },
-                              mul1) /
-                          rho;
-        const double zi = sqrt(fmax(z2, 0.0));
-        return (Z[i] < 0.0) ? -zi : zi;
+        const Ratio r = canon1(K, one, term, chunk, fold, [](const Ratio& x, const Ratio& y) {
+            return Ratio{x.prod * y.prod, 1.0, 1.0, 0};
+        });
+        z2 = r.prod / rho;
     } else {
         constexpr int M = Canon<G>::M;
-        double prod[M], pn[M], pd[M];
-        int cnt[M];
+        Ratio a[M];
 #pragma unroll
-        for (int q = 0; q < M; ++q) {
-            prod[q] = pn[q] = pd[q] = 1.0;
-            cnt[q] = 0;
-        }
-        canon_for<G>(K, sub, [&](int q, int k) {
-            const double num = (D[org[k]] - di) + tau[k];
-            double den;
-            if (k < i) den = D[k] - di;
-            else if (k < K - 1) den = D[k + 1] - di;
-            else den = 1.0;
-            pn[q] *= num;
-            pd[q] *= den;
-            if (++cnt[q] == 8) {
-                prod[q] *= pn[q] / pd[q];
-                pn[q] = 1.0;
-                pd[q] = 1.0;
-                cnt[q] = 0;
-            }
-        });
+        for (int q = 0; q < M; ++q) a[q] = one;
+        canon_for<G>(
+            K, sub, [&](int q, int k) { term(a[q], k); },
+            [&] {
 #pragma unroll
-        for (int q = 0; q < M; ++q) prod[q] *= pn[q] / pd[q];
-        const double z2 = Canon<G>::prod(prod) / rho;
-        const double zi = sqrt(fmax(z2, 0.0));
-        return (Z[i] < 0.0) ? -zi : zi;
+                for (int q = 0; q < M; ++q) chunk(a[q]);
+            });
+        double prod[M];
+#pragma unroll
+        for (int q = 0; q < M; ++q) prod[q] = a[q].prod * (a[q].pn / a[q].pd);
+        z2 = Canon<G>::prod(prod) / rho;
     }
+    const double zi = sqrt(fmax(z2, 0.0));
+    return (Z[i] < 0.0) ? -zi : zi;
 }
 
 // root_rows with canonical partial sums.
@@ -2090,37 +2097,34 @@ __device__ __forceinline__ void root_rows_c(int K, const double* __restrict__ D,
                                             const double* __restrict__ RL, const double* __restrict__ RH, int org,
                                             double tau, int sub, double* bl_out, double* bh_out) {
     const double Do = D[org];
+    auto term = [&](Sums3& a, int i) {
+        const double y = zh[i] * rcp_nr((D[i] - Do) - tau);
+        a.a = fma(y, y, a.a);
+        a.b = fma(RL[i], y, a.b);
+        a.c = fma(RH[i], y, a.c);
+    };
+    Sums3 r;
     if constexpr (G == 1) {
-        const Sums3 r = canon1(
-            [&](int q) {
-                Sums3 a{0.0, 0.0, 0.0};
-                for (int i = q; i < K; i += 16) {
-                    const double y = zh[i] * rcp_nr((D[i] - Do) - tau);
-                    a.a = fma(y, y, a.a);
-                    a.b = fma(RL[i], y, a.b);
-                    a.c = fma(RH[i], y, a.c);
-                }
-                return a;
-            },
-            add3);
-        const double inv = 1.0 / sqrt(r.a);
-        *bl_out = r.b * inv;
-        *bh_out = r.c * inv;
+        r = canon1(K, Sums3{0.0, 0.0, 0.0}, term, [](Sums3&) {}, [](Sums3&) {}, add3);
     } else {
         constexpr int M = Canon<G>::M;
-        double ss[M], bl[M], bh[M];
+        Sums3 a[M];
 #pragma unroll
-        for (int q = 0; q < M; ++q) ss[q] = bl[q] = bh[q] = 0.0;
-        canon_for<G>(K, sub, [&](int q, int i) {
-            const double y = zh[i] * rcp_nr((D[i] - Do) - tau);
-            ss[q] = fma(y, y, ss[q]);
-            bl[q] = fma(RL[i], y, bl[q]);
-            bh[q] = fma(RH[i], y, bh[q]);
-        });
-        const double inv = 1.0 / sqrt(Canon<G>::sum(ss));
-        *bl_out = Canon<G>::sum(bl) * inv;
-        *bh_out = Canon<G>::sum(bh) * inv;
+        for (int q = 0; q < M; ++q) a[q] = Sums3{0.0, 0.0, 0.0};
+        canon_for<G>(K, sub, [&](int q, int i) { term(a[q], i); });
+        auto total = [&](auto field) {
+            double p[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q) p[q] = field(a[q]);
+            return Canon<G>::sum(p);
+        };
+        r.a = total([](const Sums3& x) { return x.a; });
+        r.b = total([](const Sums3& x) { return x.b; });
+        r.c = total([](const Sums3& x) { return x.c; });
     }
+    const double inv = 1.0 / sqrt(r.a);
+    *bl_out = r.b * inv;
+    *bh_out = r.c * inv;
 }
 
 // The root steps of an in-wave level (k_level_wave): G lanes per active root
