@@ -349,56 +349,61 @@ TDE_DEV int leaf_ql(int nl, double* d, double* e, double* r0, double* r1, int st
 // denominator is formed as (D_j - D_org) - tau, so the near-pole ones carry
 // no cancellation.
 //
-// Each step fits a rational model
-//     g(x) = c + a/(0 - x) + b/(d - x)
-// (offsets from the origin pole; d the other bracketing pole) to the value and
-// slope of f at the current offset and takes its root in the bracket as the
-// next offset x (solved for x directly, not as a correction, which would
-// cancel when the root sits next to its pole).  Two fits are used:
-//  - fixed weight: the origin pole keeps its exact weight a = rho z_org^2 and
-//    the other model pole absorbs the slope of every other term;
-//  - middle way: each model pole absorbs the slope of all poles on its side.
-// Fixed weight is used first; if an iteration fails to cut |f| tenfold the
-// root switches to the middle way for good.  Safeguard: bisection of the
-// bracket.  The interior roots start from the bracket midpoint, which also
+// Each step models f around the current offset tau as
+//     g(x) = G - a/x + R s/(1 - q s),   s = x - tau
+// (offsets from the origin pole): the origin's term with its exact weight a =
+// rho z_org^2, and the rest of f (value G, slope R, q = curvature/(2 slope))
+// as a constant and one pole, which matches the rest's value and its first two
+// derivatives.  q is the mean of 1/(D_j - lambda) over the other poles,
+// weighted with their slopes, so that pole always lies outside the bracket.
+// The next offset is g's root in the bracket, solved for x directly, not as a
+// correction, which would cancel when the root sits next to its pole.
+// Safeguard: the middle of the bracket, where the model has no root in it and
+// at every other sweep after the eighth.  The interior roots start from the
+// bracket midpoint, which also
 // picks the nearer pole as origin; the last root starts from the root of the
 // equation truncated to its two nearest poles (a lower bound).
 // Stops when |f| is within its rounding-error bound, when the bracket cannot
 // shrink, or when a step is so short that the next one could not change the
-// result: of the terms a fit replaces, none has its pole nearer than the
-// origin, so their second-order error is at most (slope) step^2 / tau and the
-// new offset is within (step / tau)^2 of the root, relatively.  A model step of at
-// most kStepDone = 2^-27 of tau therefore leaves less than a quarter ulp, and
-// the sweep that would confirm it is saved.  That holds where the model's own
-// terms are no larger than a few times f's, so that rounding them stays within
-// the bound on |f| (a slope carried to a far model pole can exceed it: next to
-// a cluster of poles); there, and after a bisection, a step has to be within
+// result: none of the poles behind the rest is nearer than the origin, so the
+// model's third-order error is at most 2 (slope) |step|^3 / tau^2 and the new
+// offset is within 2 (step / tau)^3 of the root, relatively.  A model step of
+// at most kStepDone = 2^-19 of tau therefore leaves less than a quarter ulp, and
+// the sweep that would confirm it is saved; a bisection step has to be within
 // 2 ulp.  On 300000 roots of random, clustered, graded and Jacobi-like problems
-// the sweeps after the first went from 3.02 to 2.51 per root, the slowest root
-// of a merge from 5.9 to 5.2, at the same backward error (mean 0.58 against
-// 0.61 eps).  Returns the number of sweeps after the first, negative if the cap
-// was hit.
+// this takes 1.99 sweeps after the first (2.51 with a model of the rest that
+// matches value and slope alone, and 3.02 with a sweep to confirm each root),
+// the slowest root of a merge 3.2 (5.2, 5.9), at a backward error of 0.49 eps
+// (0.58, 0.61); the curvature costs one operation per term.  Returns the number
+// of sweeps after the first, negative if the cap was hit.
 // ---------------------------------------------------------------------------
-constexpr double kStepDone = 7.450580596923828125e-9;
+constexpr double kStepDone = 1.9073486328125e-6;
 
-// Root of the model in (lo, hi), or the middle of that bracket (*model =
-// false); rt = 1/tau, rd = 1/(d - tau).
-TDE_DEV double model_root(double f, double rt, double d, double rd, double a, double b, double lo, double hi,
-                          bool* model) {
-    // c(0-x)(d-x) + a(d-x) + b(0-x) = 0  <=>  c x^2 - A x + a d = 0
-    const double c = fma(a, rt, fma(-b, rd, f));
-    const double cd = c * d;
-    const double A = cd + (a + b), u = cd + (b - a);
-    // A^2 - 4 a d c = u^2 + 4 a b, a sum of positive terms
-    const double sq = sqrt_nr(fma(u, u, 4.0 * (a * b)));
-    const double den = (A >= 0.0) ? A + sq : A - sq;
-    const double r1 = den * rcp_nr(2.0 * c);
-    const double r2 = 2.0 * (a * d) * rcp_nr(den);
-    const bool in1 = c != 0.0 && r1 > lo && r1 < hi;
+// Where to look in a bracket without a usable model root: its geometric middle
+// once neither end is the origin (the offset's size is what is unknown then),
+// else its middle.
+TDE_DEV double bracket_mid(double lo, double hi) {
+    const double p = lo * hi;
+    const double g = sqrt_nr(fmax(p, 0.0));
+    return (p > 0.0) ? ((lo > 0.0) ? g : -g) : 0.5 * (lo + hi);
+}
+
+// Root of the model in (lo, hi), or bracket_mid (*model = false).
+TDE_DEV double model_root(double G, double a, double R, double q, double tau, double lo, double hi, bool* model) {
+    // (G x - a)(1 + q tau - q x) + R (x - tau) x = 0
+    const double h = fma(q, tau, 1.0);  // > 0
+    const double A2 = fma(-q, G, R);
+    const double A1 = fma(G, h, fma(a, q, -R * tau));  // A2 x^2 + A1 x - a h = 0
+    const double C = a * h;
+    const double sq = sqrt_nr(fmax(fma(A1, A1, 4.0 * A2 * C), 0.0));
+    const double den = (A1 >= 0.0) ? -A1 - sq : sq - A1;
+    const double r1 = den * rcp_nr(2.0 * A2);
+    const double r2 = -2.0 * C * rcp_nr(den);
+    const bool in1 = A2 != 0.0 && r1 > lo && r1 < hi;
     const bool in2 = den != 0.0 && r2 > lo && r2 < hi;
     *model = in1 != in2;
     const double one = in2 ? r2 : r1;
-    const double mid = 0.5 * (lo + hi);
+    const double mid = bracket_mid(lo, hi);
     return (in1 && in2) ? 0.5 * (r1 + r2) : ((in1 || in2) ? one : mid);
 }
 
@@ -410,25 +415,22 @@ struct RedSerial {
     TDE_DEV static double prod(double x) { return x; }
 };
 
-// Sums of one pole sweep, the excluded poles left out: t_j = w_j/(D_j - lambda)
-// (w_j = z_j^2), its slope t_j/(D_j - lambda), and the same with |t_j|.  A pole
-// left of the root has t < 0, a right one t > 0, so the signed and the
-// absolute sums give both sides' totals, and |t| costs nothing (an operand
-// modifier) where a split by side would take two more operations per term.
+// Sums of one pole sweep, the excluded poles left out, with r_j = 1/(D_j -
+// lambda) and t_j = z_j^2 r_j: value, slope, half the curvature, and the sum of
+// absolute terms (an operand modifier, not an operation) that bounds the value's
+// rounding.
 struct SecSums {
-    double t, dt;    // sum of t, of t/(D - lambda)
-    double at, adt;  // sum of |t|, of |t|/(D - lambda)
+    double t, dt, ct;  // sum of t, t r, t r^2
+    double at;         // sum of |t|
 };
 
 // State of one secular root between pole sweeps.
 struct SecRoot {
     int o;               // origin pole
     double lo, hi, tau;  // bracket and current offset from D_o
-    double d;            // the other bracketing pole relative to D_o
     double zo, wo;       // z_o and the origin weight rho z_o^2
-    double fprev;
+    int n;               // sweeps so far
     bool orgl;           // origin is the left bracketing pole
-    bool fixed_weight;
 };
 
 // Interior root k < K-1 (kk = k): from the sums at the bracket midpoint with
@@ -448,18 +450,18 @@ TDE_DEV bool sec_start_interior(int k, const double* __restrict__ D, const doubl
     r->lo = r->orgl ? 0.0 : -mid;
     r->hi = r->orgl ? mid : 0.0;
     r->tau = r->orgl ? mid : -mid;
-    r->d = r->orgl ? gap : -gap;
     r->zo = r->orgl ? zl : zr;
     r->wo = rho * r->zo * r->zo;
-    r->fixed_weight = true;
-    r->fprev = INFINITY;
+    r->n = 0;
     if (f == 0.0) return true;
-    // the other pole is as far from the midpoint as the origin: 1/(d - tau) = 1/tau
-    const double ao = r->orgl ? ar : al;
-    const double b = mid * mid * rho * fma(ao, ao, s.dt);
-    const double rt = r->orgl ? rm : -rm;
+    // the rest of f: the sums and the other bracketing pole
+    const double ao = r->orgl ? ar : al;       // its sqrt(slope)
+    const double so = ao * ao, ro = r->orgl ? rm : -rm;
+    const double sl = s.dt + so;
+    const double q = fma(so, ro, s.ct) * rcp_nr(sl);
+    const double G = fma(rho, s.t + (r->orgl ? zr * ar : zl * al), 1.0);
     bool model;
-    r->tau = model_root(f, rt, r->d, rt, r->wo, b, r->lo, r->hi, &model);
+    r->tau = model_root(G, r->wo, rho * sl, q, r->tau, r->lo, r->hi, &model);
     return false;
 }
 
@@ -475,12 +477,10 @@ TDE_DEV void sec_start_last(int K, const double* __restrict__ D, const double* _
     const double b = g - w1 - w2, sq = sqrt_nr(b * b + 4.0 * w1 * g);
     const double t2 = (b <= 0.0) ? 0.5 * (sq - b) : 2.0 * w1 * g * rcp_nr(b + sq);
     r->tau = (t2 > r->lo && t2 < r->hi) ? t2 : 0.5 * r->hi;
-    r->d = dk - dk1;
     r->zo = Z[K - 1];
     r->wo = rho * r->zo * r->zo;
     r->orgl = false;
-    r->fixed_weight = true;
-    r->fprev = INFINITY;
+    r->n = 0;
 }
 
 // One iteration from a sweep at r->tau (the origin excluded from its sums).
@@ -488,29 +488,22 @@ TDE_DEV void sec_start_last(int K, const double* __restrict__ D, const double* _
 // r->tau.
 TDE_DEV int sec_update(SecRoot* r, double rho, const SecSums& s) {
     const double tau = r->tau;
-    const double g = r->d - tau;
-    const double rt = rcp_nr(tau), rd = rcp_nr(g);
-    const double to = -r->zo * rt;
-    const double termo = r->zo * to, dto = to * to;
-    const double f = fma(rho, s.t + termo, 1.0);
+    const double termo = -r->zo * (r->zo * rcp_nr(tau));
+    const double G = fma(rho, s.t, 1.0);
+    const double f = fma(rho, termo, G);
     const double size = fma(rho, s.at + fabs(termo), 1.0);  // f's terms
     if (fabs(f) <= 8.0 * DBL_EPSILON * size) return 1;
     if (f < 0.0) r->lo = tau;
     else r->hi = tau;
     if (r->hi - r->lo <= 2.0 * DBL_EPSILON * fmax(fabs(r->lo), fabs(r->hi))) return 1;
-    if (r->fixed_weight && fabs(f) > 0.1 * fabs(r->fprev)) r->fixed_weight = false;
-    r->fprev = f;
-    // slopes of the origin's side and of the other one (middle way), or of
-    // everything but the origin against the other pole (fixed weight)
-    const double h = r->orgl ? -s.adt : s.adt;
-    const double so = fmax(0.5 * (s.dt + h), 0.0), st = fmax(0.5 * (s.dt - h), 0.0);
-    const double a = r->fixed_weight ? r->wo : tau * tau * rho * (so + dto);
-    const double b = g * g * rho * (r->fixed_weight ? s.dt : st);
     bool model;
-    const double tn = model_root(f, rt, r->d, rd, a, b, r->lo, r->hi, &model);
+    double tn = model_root(G, r->wo, rho * s.dt, s.ct * rcp_nr(s.dt), tau, r->lo, r->hi, &model);
+    if (++r->n > 8 && (r->n & 1)) {
+        tn = bracket_mid(r->lo, r->hi);
+        model = false;
+    }
     r->tau = tn;
-    const bool sound = model && fmax(fabs(a * rt), fabs(b * rd)) <= 4.0 * size;
-    if (fabs(tn - tau) <= (sound ? kStepDone : 2.0 * DBL_EPSILON) * fabs(tau)) return 1;
+    if (fabs(tn - tau) <= (model ? kStepDone : 2.0 * DBL_EPSILON) * fabs(tau)) return 1;
     return 0;
 }
 
@@ -525,11 +518,11 @@ TDE_DEV double weight_unless(bool drop, double x) {
 // One term of a sweep, added to s.
 TDE_DEV void sec_term(double dj, double wj, double Do, double tau, SecSums* s) {
     const double r = rcp_nr((dj - Do) - tau);
-    const double t = wj * r;
+    const double t = wj * r, u = t * r;
     s->t += t;
-    s->dt = fma(t, r, s->dt);
+    s->dt += u;
+    s->ct = fma(u, r, s->ct);
     s->at += fabs(t);
-    s->adt = fma(fabs(t), r, s->adt);
 }
 
 // One pole sweep for a root at offset tau from pole Do: every pole but those
@@ -578,8 +571,8 @@ TDE_DEV void sec_sweep(int K, const double* __restrict__ D, const double* __rest
     for (; j < K; j += G) term(j, D[j], W[j]);
     s->t = Red::sum(a.t);
     s->dt = Red::sum(a.dt);
+    s->ct = Red::sum(a.ct);
     s->at = Red::sum(a.at);
-    s->adt = Red::sum(a.adt);
     if (ZZ) *zz = Red::sum(z);
 }
 

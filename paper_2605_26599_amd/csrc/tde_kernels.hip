@@ -1066,21 +1066,24 @@ __device__ __forceinline__ void far_moments(int j0, int j1, int j2, int j3, doub
     __syncthreads();
 }
 
-// The polynomial sum_k coef[k] t^k and its derivative by t.
+// The polynomial sum_k coef[k] t^k, and with its first derivative by t and half
+// its second one.
 __device__ __forceinline__ double far_value(const double* coef, double t) {
     double s = coef[kFarTerms - 1];
 #pragma unroll
     for (int k = kFarTerms - 2; k >= 0; --k) s = fma(s, t, coef[k]);
     return s;
 }
-__device__ __forceinline__ double far_value(const double* coef, double t, double* ds) {
-    double s = coef[kFarTerms - 1], d = 0.0;
+__device__ __forceinline__ double far_value(const double* coef, double t, double* d1, double* d2) {
+    double s = coef[kFarTerms - 1], d = 0.0, c = 0.0;
 #pragma unroll
     for (int k = kFarTerms - 2; k >= 0; --k) {
+        c = fma(c, t, d);
         d = fma(d, t, s);
         s = fma(s, t, coef[k]);
     }
-    *ds = d;
+    *d1 = d;
+    *d2 = c;
     return s;
 }
 
@@ -1115,8 +1118,8 @@ __device__ __forceinline__ int wide_last_root(int K, const double* __restrict__ 
         _Pragma("unroll 4") for (int j = threadIdx.x; j < K - 1; j += NW * 64) sec_term(D[j], W[j], Do, r->tau, &s);
         s.t = wide_total<NW>(s.t, red);
         s.dt = wide_total<NW>(s.dt, red);
+        s.ct = wide_total<NW>(s.ct, red);
         s.at = -s.t;  // every pole lies to the left
-        s.adt = -s.dt;
         if (sec_update(r, rho, s)) return it;
     }
     return -1;
@@ -1190,18 +1193,17 @@ __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, 
                 SecSums u{0.0, 0.0, 0.0, 0.0};
                 wide_sweep(Dc, Wc, a, b, w0, w1, Do, tau, L1, R0, u);
                 if (fw.far && wv < 2) {
-                    double ds;
-                    const double v = far_value(coef + wv * kFarFold, ((Do - fw.c) + tau) * fw.rh, &ds);
-                    ds *= fw.rh;
+                    double d1, d2;
+                    const double v = far_value(coef + wv * kFarFold, ((Do - fw.c) + tau) * fw.rh, &d1, &d2);
                     u.t += v;
-                    u.dt += ds;
-                    u.at += (wv == 0) ? -v : v;
-                    u.adt += (wv == 0) ? -ds : ds;
+                    u.dt = fma(d1, fw.rh, u.dt);
+                    u.ct = fma(d2, fw.rh * fw.rh, u.ct);
+                    u.at += fabs(v);
                 }
                 R4(buf, 0, wv) = u.t;
                 R4(buf, 1, wv) = u.dt;
-                R4(buf, 2, wv) = u.at;
-                R4(buf, 3, wv) = u.adt;
+                R4(buf, 2, wv) = u.ct;
+                R4(buf, 3, wv) = u.at;
                 __syncthreads();
                 auto total = [&](int q) {
                     double x = 0.0;
@@ -1210,8 +1212,8 @@ __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, 
                 };
                 tot.t = total(0);
                 tot.dt = total(1);
-                tot.at = total(2);
-                tot.adt = total(3);
+                tot.ct = total(2);
+                tot.at = total(3);
                 buf ^= 1;
             };
             // first sweep: bracket midpoint with origin kk
@@ -1961,7 +1963,7 @@ __device__ __forceinline__ void sec_sweep_c(int K, const double* __restrict__ D,
     if constexpr (G == 1) {
         *s = canon1(K, SecSums{0.0, 0.0, 0.0, 0.0}, term, [](SecSums&) {}, [](SecSums&) {},
                     [](const SecSums& x, const SecSums& y) {
-                        return SecSums{x.t + y.t, x.dt + y.dt, x.at + y.at, x.adt + y.adt};
+                        return SecSums{x.t + y.t, x.dt + y.dt, x.ct + y.ct, x.at + y.at};
                     });
     } else {
         constexpr int M = Canon<G>::M;
@@ -1977,8 +1979,8 @@ __device__ __forceinline__ void sec_sweep_c(int K, const double* __restrict__ D,
         };
         s->t = total([](const SecSums& x) { return x.t; });
         s->dt = total([](const SecSums& x) { return x.dt; });
+        s->ct = total([](const SecSums& x) { return x.ct; });
         s->at = total([](const SecSums& x) { return x.at; });
-        s->adt = total([](const SecSums& x) { return x.adt; });
     }
 }
 
