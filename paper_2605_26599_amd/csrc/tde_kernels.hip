@@ -975,17 +975,23 @@ __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b,
 // A root next to a pole sees that pole among the near ones, as exactly as
 // before.  Fewer than kFarMin far poles are swept directly.
 //
-// kFarRatio and kFarTerms: the far poles cost 2 kFarTerms operations per pole
-// and block, the near ones 13 per pole, root and sweep; ratio 4 with 28 terms
-// balances the two at K of a few ten thousand.
-// Measured (Toeplitz n = 65536, seven wide levels, K up to 32768, against
-// sweeps over all poles, which were FP64-issue-bound at 33% of the peak):
-// secular 9.22 -> 0.78 ms, Loewner 1.75 -> 0.44, rows 1.61 -> 0.61, the solve
-// 13.7 -> 3.13 ms, its largest error unchanged (5e-16 of the spectrum's norm).
+// kFarRatio and kFarTerms: a far pole costs 37 operations and its reciprocal
+// per block, a near one about 13 per pole, root and sweep; ratio 4 with 28
+// terms balances the two at K of a few ten thousand.  Poles with |u| <= 1/12
+// leave as little after 16 terms and those with |u| <= 1/128 after 8, so most
+// of a large merge's poles (consecutive ones, 64 to a wave, so nearly every
+// wave agrees) stop there.
+// Measured (Toeplitz n = 65536, seven wide levels, K up to 65536): sweeps over
+// all poles were FP64-issue-bound at 33% of the peak, 13.7 ms the solve; with
+// 28 terms (56 operations) for every far pole secular 0.64, Loewner 0.45, rows
+// 0.61 and 2.41 ms, still issue-bound; with shorter sums 0.57, 0.40, 0.47 and
+// 2.15 ms.  The solve's largest error is unchanged (5e-16 of the spectrum's
+// norm or less).
 // ---------------------------------------------------------------------------
 constexpr int kFarTerms = 28;
 constexpr int kFarFold = 32;  // kFarTerms padded to the fold's power of two
 constexpr double kFarRatio = 4.0;
+constexpr double kFarHalf = 1.0 / 12.0, kFarShort = 1.0 / 128.0;
 constexpr int kFarMin = 192;
 // LDS of the expansions: NW folded partials and two coefficient sets.
 constexpr int far_lds(int nw) { return (nw + 2) * kFarFold; }
@@ -1057,6 +1063,61 @@ __device__ __forceinline__ double wave_fold(double (&m)[kFarFold]) {
     return m[0] + __shfl_xor(m[0], 1, 64);
 }
 
+// Adds v u^k to m[k] for the k that count: four moments per step of u^4 (37
+// operations for 28 moments instead of the 56 of taking each power from the
+// last one), 8 or 16 moments where every lane's u is small enough.
+__device__ __forceinline__ void far_add(double (&m)[kFarFold], double v, double u) {
+    const double au = fabs(u);
+    const double u2 = u * u, u3 = u2 * u, u4 = u2 * u2;
+    auto four = [&](int k) {
+        m[k] += v;
+        m[k + 1] = fma(v, u, m[k + 1]);
+        m[k + 2] = fma(v, u2, m[k + 2]);
+        m[k + 3] = fma(v, u3, m[k + 3]);
+        v *= u4;
+    };
+    four(0);
+    four(4);
+    if (__any(au > kFarShort)) {
+        four(8);
+        four(12);
+        if (__any(au > kFarHalf)) {
+            four(16);
+            four(20);
+            four(24);
+        }
+    }
+}
+// Adds u^(k+1) - v^(k+1) to m[k], du = u - v, by
+// u^(k+j) - v^(k+j) = u^j (u^k - v^k) + v^k (u^j - v^j).
+__device__ __forceinline__ void far_add_log(double (&m)[kFarFold], double u, double v, double du) {
+    const double au = fmax(fabs(u), fabs(v));
+    const double u2 = u * u, v2 = v * v, u3 = u2 * u, u4 = u2 * u2, v4 = v2 * v2;
+    const double d2 = du * (u + v), d3 = fma(u, d2, v2 * du), d4 = d2 * (u2 + v2);
+    double em = du;  // u^(k+1) - v^(k+1)
+    double vm = v;   // v^(k+1)
+    auto four = [&](int k) {
+        m[k] += em;
+        m[k + 1] = fma(u, em, fma(vm, du, m[k + 1]));
+        m[k + 2] = fma(u2, em, fma(vm, d2, m[k + 2]));
+        m[k + 3] = fma(u3, em, fma(vm, d3, m[k + 3]));
+        em = fma(u4, em, vm * d4);
+        vm *= v4;
+    };
+    four(0);
+    four(4);
+    if (__any(au > kFarShort)) {
+        four(8);
+        four(12);
+        if (__any(au > kFarHalf)) {
+            four(16);
+            four(20);
+            four(24);
+        }
+    }
+}
+static_assert(kFarTerms == 28, "far_add and far_add_log write the steps out");
+
 // Moments over the workgroup: term(j, v, u) gives pole j's first moment v and
 // its ratio u (moment k is the sum of v u^k); j runs over [0, n0) and [n1, K)
 // when both is set, else over [j0, j1) alone.  The kFarTerms totals land in
@@ -1072,11 +1133,7 @@ __device__ __forceinline__ void far_moments(int j0, int j1, int j2, int j3, doub
         const int j = (q < nl) ? j0 + q : j2 + (q - nl);
         double v, u;
         term(j, &v, &u);
-#pragma unroll
-        for (int k = 0; k < kFarTerms; ++k) {
-            m[k] += v;
-            v *= u;
-        }
+        far_add(m, v, u);
     }
     const double tot = wave_fold(m);
     if ((lane & 1) == 0) part[wv * kFarFold + (lane >> 1)] = tot;
@@ -1372,15 +1429,8 @@ __device__ void lowner_wide(int bid, int nbw, const MergeRec* __restrict__ mr, i
                     }
                     const double rl = rcp_nr(dl), rd = rcp_nr(dd);
                     const double u = fw.h * rd, v = fw.h * rl;
-                    double vm = u * (((dor - Dk) + tk) * rl);  // v^m (u - v)
-                    double em = vm;                            // u^m - v^m
-                    mm[0] += em;
-#pragma unroll
-                    for (int x = 1; x < kFarTerms; ++x) {
-                        vm *= v;
-                        em = fma(u, em, vm);
-                        mm[x] += em;
-                    }
+                    const double du = u * (((dor - Dk) + tk) * rl);  // u - v
+                    far_add_log(mm, u, v, du);
                 }
                 prod *= pn / pd;
                 for (int o = 32; o > 0; o >>= 1) prod *= __shfl_xor(prod, o, 64);
