@@ -1232,7 +1232,11 @@ __device__ void secular_wide(int bid, int nbw, const MergeRec* __restrict__ mr, 
     int buf = 0;
     int bad = 0;
     unsigned long long terms = 0, sweeps = 0, roots = 0;
-    for (int item = bid; item < total; item += nbw) {
+    for (int q = bid; q < total; q += nbw) {
+        // from the top down: the last block of a merge also has its last root,
+        // and was among the last to start (Toeplitz n = 65536: the largest
+        // launch 162 -> 130 us, the solve 2.15 -> 2.09 ms)
+        const int item = total - 1 - q;
         const int m = wide_merge_of(items, M, item);
         const MergeRec R = mr[m];
         const MergeSpan sp = merge_span(R, w.scan);
@@ -1516,7 +1520,8 @@ __device__ void rows_wide(int bid, int nbw, const MergeRec* __restrict__ mr, int
     double* coef = part + NW * kFarFold;
     const int total = items[M];
     unsigned long long pairs = 0;
-    for (int item = bid; item < total; item += nbw) {
+    for (int q = bid; q < total; q += nbw) {
+        const int item = total - 1 - q;  // as secular_wide
         const int m = wide_merge_of(items, M, item);
         const MergeRec R = mr[m];
         if (!(R.flags & MF_ROOT) || w.rows_out) {
