@@ -238,24 +238,32 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafRec* __restrict__ leaves,
 constexpr int kDcCols = kLeafMax;  // columns of one in-wave leaf
 static_assert(kDcCols == 64, "one lane per column of an in-wave leaf");
 
-// LDS of one in-wave level: 18 double arrays of kDcCols entries (21 with the
-// node state), 7 int arrays of kDcCols (+1) entries and the level's merge
+// LDS of one in-wave level: 12 double arrays of kDcCols entries (15 with the
+// node state), 5 int arrays of kDcCols (+1) entries and the level's merge
 // records (at most kDcCols / 2: every merge has two or more columns).
 template <bool Nodes>
 struct WaveLds {
-    double b[(Nodes ? 21 : 18) * kDcCols];
-    int i[3 * kDcCols + 4 * (kDcCols + 1)];
+    double b[(Nodes ? 15 : 12) * kDcCols];
+    int i[2 * kDcCols + 3 * (kDcCols + 1)];
     MergeRec smr[kDcCols / 2];
 };
+// 16 waves on a compute unit's 160 KB, as many as the registers allow.
+static_assert(sizeof(WaveLds<true>) <= 160 * 1024 / 16, "LDS of an in-wave leaf");
 
 // Level arrays of an in-wave level in LDS.  A level runs merge | flags | runs |
 // three-way split | roots | Loewner | rows | assembly; the merged and rotated
 // columns (D, Z, RL, RH, D2, Z2) are last read by the split, so the later
 // steps' arrays live in them: active z (split to Loewner) in Z, tau in D, the
 // root values in D2, z-hat in Z2, the parent rows in RL and RH; the roots'
-// origins reuse the candidate positions, last read by the runs.  Fewer arrays
-// let more waves share a compute unit.  With Nodes, the node state lam, blo,
-// bhi gets LDS storage too.
+// origins reuse the candidate positions, last read by the runs, the rotated
+// counts the candidate counts, and the active columns' merges the child
+// indices, which no step of a wave reads.  The active, the rotated and the
+// negligible columns are N in all, so the three lists follow one another in
+// one array each (wave_lists, once their lengths are known).  Fewer arrays let
+// more waves share a compute unit, whose LDS held 12 in-wave leaves or 13
+// packs with lists of their own; 16 now (the leaves of normal n = 262144 282 ->
+// 225 us, the packs of a batch of 4096 problems of 32 to 4096 columns 2.59 ->
+// 2.30 ms).  With Nodes, the node state lam, blo, bhi gets LDS storage too.
 template <bool Nodes>
 __device__ __forceinline__ void wave_arrays(WaveLds<Nodes>& sh, Work& wl) {
     constexpr int C = kDcCols;
@@ -266,13 +274,17 @@ __device__ __forceinline__ void wave_arrays(WaveLds<Nodes>& sh, Work& wl) {
     wl.D = p; p += C;    wl.Z = p; p += C;    wl.RL = p; p += C;   wl.RH = p; p += C;
     wl.D2 = p; p += C;   wl.Z2 = p; p += C;   wl.RL2 = p; p += C;  wl.RH2 = p; p += C;
     wl.Da = p; p += C;   wl.Wa = p; p += C;   wl.RLa = p; p += C;  wl.RHa = p; p += C;
-    wl.Dd = p; p += C;   wl.RLd = p; p += C;  wl.RHd = p; p += C;
-    wl.Dr = p; p += C;   wl.RLr = p; p += C;  wl.RHr = p; p += C;
     wl.Za = wl.Z;        wl.tau = wl.D;       wl.rootval = wl.D2;  wl.zhat = wl.Z2;
     wl.PBL = wl.RL;      wl.PBH = wl.RH;
     int* q = sh.i;
-    wl.src = q; q += C;  wl.nnpos = q; q += C;  wl.amerge = q; q += C;  wl.org = wl.nnpos;
-    wl.st = q; q += C + 1;  wl.scan = q; q += C + 1;  wl.scanC = q; q += C + 1;  wl.scanR = q; q += C + 1;
+    wl.src = q; q += C;  wl.nnpos = q; q += C;  wl.amerge = wl.src;  wl.org = wl.nnpos;
+    wl.st = q; q += C + 1;  wl.scan = q; q += C + 1;  wl.scanC = q; q += C + 1;  wl.scanR = wl.scanC;
+}
+// The rotated and the negligible columns' lists, behind the K active and the
+// nr rotated columns.
+__device__ __forceinline__ void wave_lists(Work& wl, int K, int nr) {
+    wl.Dr = wl.Da + K;    wl.RLr = wl.RLa + K;  wl.RHr = wl.RHa + K;
+    wl.Dd = wl.Dr + nr;   wl.RLd = wl.RLr + nr; wl.RHd = wl.RHr + nr;
 }
 
 // Work done by the in-wave levels of one wave (for the counters).
@@ -304,8 +316,8 @@ __device__ void wave_roots_canon(const MergeRec* smr, int K, const double* __res
 // per root sums serially.
 template <int CG>
 __device__ __forceinline__ void wave_level(const MergeRec* smr, int M, int N, const double* __restrict__ e,
-                                           const unsigned long long* __restrict__ pmax, const Work& wl,
-                                           const Work& wt, bool top, double* __restrict__ out,
+                                           const unsigned long long* __restrict__ pmax, Work& wl,
+                                           Work& wt, bool top, double* __restrict__ out,
                                            int* __restrict__ corg, double* __restrict__ ctau, long long pk0,
                                            WaveCount& c) {
     const int lane = threadIdx.x & 63;
@@ -335,6 +347,9 @@ __device__ __forceinline__ void wave_level(const MergeRec* smr, int M, int N, co
     const unsigned long long am = __ballot(lane < N && s == 1);
     const unsigned long long rm = __ballot(lane < N && s == 2);
     const int g = (int)__popcll(am & below), gr = (int)__popcll(rm & below);
+    const int K = (int)__popcll(am);
+    wave_lists(wl, K, (int)__popcll(rm));
+    wave_lists(wt, K, (int)__popcll(rm));
     if (lane < N) {
         wl.scan[lane] = g;
         wl.scanR[lane] = gr;
@@ -358,12 +373,11 @@ __device__ __forceinline__ void wave_level(const MergeRec* smr, int M, int N, co
         }
     }
     if (lane == 0) {
-        wl.scan[N] = (int)__popcll(am);
+        wl.scan[N] = K;
         wl.scanR[N] = (int)__popcll(rm);
     }
     __syncthreads();
     // secular roots, Loewner z, boundary rows
-    const int K = (int)__popcll(am);
     if constexpr (CG > 0) {
         wave_roots_canon<CG>(smr, K, e, pmax, wl, corg, ctau, pk0, c);
         if (lane < N) body_assemble(lane, find_merge(smr, M, lane), smr, pmax, wl, out);
