@@ -1889,8 +1889,11 @@ __global__ __launch_bounds__(NW * 64) void k_secular_wide(const MergeRec* __rest
 }
 
 // The same for the Loewner step and the rows (forward pass).
+// (four waves per SIMD: beyond 128 registers only one workgroup of eight waves
+// would fit a compute unit; the 18 registers spilt cost less than the idle
+// half.  Toeplitz n = 65536: 400 -> 332 us per solve)
 template <int NW>
-__global__ __launch_bounds__(NW * 64) void k_lowner_wide(const MergeRec* __restrict__ mr, int M,
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_lowner_wide(const MergeRec* __restrict__ mr, int M,
                                                          const double* __restrict__ e,
                                                          const unsigned long long* __restrict__ pmax, Work w) {
     if (input_nonfinite(w)) return;
