@@ -522,10 +522,9 @@ __global__ __launch_bounds__(64) void k_leaf_dc(const LeafRec* __restrict__ leav
 // few terms there), four on merges of up to 64.
 // ---------------------------------------------------------------------------
 template <int G>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_level_wave(const MergeRec* __restrict__ mr, const int* __restrict__ packs,
-                                                  const double* __restrict__ e,
-                                                  const unsigned long long* __restrict__ pmax, Work w,
-                                                  double* __restrict__ out, int save_roots) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_level_wave(
+    const MergeRec* __restrict__ mr, const int* __restrict__ packs, const double* __restrict__ e,
+    const unsigned long long* __restrict__ pmax, Work w, double* __restrict__ out, int save_roots) {
     if (input_nonfinite(w)) return;
     __shared__ WaveLds<false> sh;
     const int lane = threadIdx.x;
@@ -612,8 +611,8 @@ __global__ __launch_bounds__(kWG) void k_merge(const MergeRec* __restrict__ mr, 
     }
 }
 
-// The same by output position (merge path), for levels of large merges: block b writes packed positions
-// [b kWG, (b+1) kWG).  For each merge piece the block covers, the co-ranks
+// The same by output position (merge path), for levels of large merges: block
+// b writes packed positions [b kWG, (b+1) kWG).  For each merge piece the block covers, the co-ranks
 // of the piece's two ends (how many left-child values precede them) are found
 // cooperatively, half the block per end, 128 probes a round, so a merge of
 // s columns needs about log_128(s) dependent global reads instead of log2(s)
@@ -730,8 +729,9 @@ __global__ __launch_bounds__(kWG) void k_nncompact(long long N, Work w, int self
 // Close-pole runs over the candidates (grid-stride).  Each rotated-away
 // column moves one count from its block's active tally to its rotated tally;
 // a workgroup's candidates are consecutive, so it gathers the counts of the
-// kRunBins blocks from its first candidate's on in LDS (Toeplitz n = 65536, where half the
-// columns rotate: 32768 pairs of atomics on 512 words: 39 us per level, 6.4 us now).
+// kRunBins blocks from its first candidate's on in LDS (Toeplitz n = 65536,
+// where half the columns rotate: 32768 pairs of atomics on 512 words took 39 us
+// per level, 6.4 us now).
 constexpr int kRunBins = 64;
 __global__ __launch_bounds__(kWG) void k_runs(const MergeRec* __restrict__ mr, const int* __restrict__ blkm,
                                               long long N, Work w) {
@@ -1893,9 +1893,9 @@ __global__ __launch_bounds__(NW * 64) void k_secular_wide(const MergeRec* __rest
 // would fit a compute unit; the 18 registers spilt cost less than the idle
 // half.  Toeplitz n = 65536: 400 -> 332 us per solve)
 template <int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_lowner_wide(const MergeRec* __restrict__ mr, int M,
-                                                         const double* __restrict__ e,
-                                                         const unsigned long long* __restrict__ pmax, Work w) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_lowner_wide(
+    const MergeRec* __restrict__ mr, int M, const double* __restrict__ e, const unsigned long long* __restrict__ pmax,
+    Work w) {
     if (input_nonfinite(w)) return;
     __shared__ double red[wide_lowner_lds(NW)];
     lowner_wide<NW, true>((int)blockIdx.x, (int)gridDim.x, mr, M, e, pmax, w, false, w.witems, red);
