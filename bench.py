@@ -629,7 +629,7 @@ def dense_record(tde, dev, n=4096, reps=3):
     tri()
     tt = timed(tri, reps) / reps
     m = np.arange(n - 2, 0, -1, dtype=np.float64)
-    sym_bytes = float(8.0 * np.sum(m * m))
+    sym_bytes = float(4.0 * np.sum(m * (m + 1)))  # the lower triangle once per column
     err = float(np.abs(out - lam).max())
     norm1 = float(np.abs(A).sum(axis=0).max())
     return {"workload": f"dense symmetric n={n}, prescribed spectrum U(-1,1), seeded random orthogonal Q",

@@ -998,8 +998,8 @@ __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b,
 // Measured (Toeplitz n = 65536, seven wide levels, K up to 65536): sweeps over
 // all poles were FP64-issue-bound at 33% of the peak, 13.7 ms the solve; with
 // 28 terms (56 operations) for every far pole secular 0.64, Loewner 0.45, rows
-// 0.61 and 2.41 ms, still issue-bound; with shorter sums 0.57, 0.40, 0.47 and
-// 2.15 ms.  The solve's largest error is unchanged (5e-16 of the spectrum's
+// 0.61 and 2.41 ms; with shorter sums 0.57, 0.40, 0.47 and 2.15 ms, at 14 to 19%
+// of the peak, bound by load latency at two workgroups per compute unit.  The solve's largest error is unchanged (5e-16 of the spectrum's
 // norm or less).
 // ---------------------------------------------------------------------------
 constexpr int kFarTerms = 28;
