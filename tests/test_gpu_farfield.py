@@ -85,3 +85,17 @@ def test_far_field_rows(tde, n):
         assert np.abs(lam - lr).max() <= 256.0 * EPS * tdgen.tnorm1(d, e)
         assert np.all(np.abs(q0 - np.abs(r0)) <= tol)
         assert np.all(np.abs(q0 * q1 - r0 * r1) <= tol)
+
+
+@pytest.mark.parametrize("n", [9000, 20001])
+def test_far_field_distant(tde, n):
+    """Merges with poles beyond 128 half-widths of a block, whose moments stop
+    at eight terms (half of a Toeplitz merge's columns stay active), against
+    4 sin^2(k pi / (2 (n + 1))); ten levels: 240 eps ||T||_1."""
+    d, e = np.full(n, 2.0), np.full(n - 1, -1.0)
+    ref = 4.0 * np.sin(np.arange(1, n + 1) * np.pi / (2.0 * (n + 1))) ** 2
+    for wide_min, fuse_few in [(2, 2), (600, 64)]:
+        print(f"[gpu-far] distant n={n} wide_min={wide_min}", flush=True)
+        lam = tde.eigvals(_t(d), _t(e), wide_min=wide_min, fuse_few=fuse_few).cpu().numpy()
+        assert np.all(np.diff(lam) >= 0.0)
+        assert np.abs(lam - ref).max() <= 256.0 * EPS * 4.0
