@@ -188,14 +188,14 @@ __global__ __launch_bounds__(kWG) void k_maxabs(const double* __restrict__ d, co
         sv[wv] = vc;
     }
     __syncthreads();
-    bool block_one = true;
+    bool block_one = sb[0] >= 0;  // (four waves over several problems each agree on -2)
     unsigned long long vb = 0;
     for (int q = 0; q < kWG / 64; ++q) {
         block_one = block_one && (sb[q] == sb[0]);
         vb = (sv[q] > vb) ? sv[q] : vb;
     }
     if (block_one) {
-        if (threadIdx.x == 0 && sb[0] >= 0) atomicMax(&pmax[sb[0]], vb);
+        if (threadIdx.x == 0) atomicMax(&pmax[sb[0]], vb);
     } else if (wave_one) {
         if (lane == 0 && b0 >= 0) atomicMax(&pmax[b0], vc);
     } else if (bc >= 0) {
