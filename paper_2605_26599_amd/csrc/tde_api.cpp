@@ -44,12 +44,13 @@ struct PlanEntry {
 std::list<PlanEntry> g_plan_lru;  // front = most recently used
 std::map<PlanKey, std::list<PlanEntry>::iterator> g_plans;
 
-// Captured passes: one executable graph per (plan, pass kind, buffers).
+// Captured passes: one executable graph per (plan, pass kind, secular sweep
+// cap, buffers): everything that a captured launch holds by value.
 // Capture runs on an internal stream per device; replays run on the
 // caller's stream.
 enum { PASS_SOLVE = 0, PASS_CKPT = 1, PASS_BACKWARD = 2, PASS_ROWS = 3, PASS_DENSE = 4 };
 using Bufs = std::array<const void*, 8>;
-using GraphKey = std::tuple<const Plan*, int, Bufs>;
+using GraphKey = std::tuple<const Plan*, int, int, Bufs>;
 constexpr size_t kMaxGraphs = 64;
 struct GraphEntry {
     GraphKey key;
@@ -118,9 +119,9 @@ void evict_plan(std::list<PlanEntry>::iterator it) {
 }
 
 // Caller holds g_mu.
-int graph_for(const Plan& plan, int kind, const Bufs& bufs, const std::function<int(void*)>& enqueue,
+int graph_for(const Plan& plan, int kind, int cap, const Bufs& bufs, const std::function<int(void*)>& enqueue,
               GraphEntry** out) {
-    GraphKey key{&plan, kind, bufs};
+    GraphKey key{&plan, kind, cap, bufs};
     auto it = g_graphs.find(key);
     if (it != g_graphs.end()) {
         g_graph_lru.splice(g_graph_lru.begin(), g_graph_lru, it->second);
@@ -165,13 +166,14 @@ int graph_for(const Plan& plan, int kind, const Bufs& bufs, const std::function<
 }
 
 // Runs enqueue either eagerly on the caller's stream or through the graph
-// cache, as the options and timing mode ask.
-int run_pass(const Plan& plan, int kind, const Bufs& bufs, const tde_opts* opts, void* stream,
+// cache, as the options and timing mode ask.  cap: the pass's secular sweep
+// cap, 0 for passes that solve no roots.
+int run_pass(const Plan& plan, int kind, int cap, const Bufs& bufs, const tde_opts* opts, void* stream,
              const std::function<int(void*)>& enqueue) {
     const bool use_graph = !(opts && (opts->flags & TDE_FLAG_NO_GRAPH)) && !timing_enabled();
     if (use_graph) {
         GraphEntry* ge = nullptr;
-        const int rc = graph_for(plan, kind, bufs, enqueue, &ge);
+        const int rc = graph_for(plan, kind, cap, bufs, enqueue, &ge);
         if (rc != TDE_OK) return rc;
         if (hipGraphLaunch(ge->exec, (hipStream_t)stream) != hipSuccess) return TDE_EDEVICE;
         return hipEventRecord(ge->done, (hipStream_t)stream) == hipSuccess ? TDE_OK : TDE_EDEVICE;
@@ -325,18 +327,18 @@ int solve(const double* d, const double* e, const std::vector<long long>& offs, 
         w.qlast = qlast;
         w.rows_out = 1;
         Bufs bufs{d, e, lambda, ws, qfirst, qlast, nullptr, nullptr};
-        return run_pass(*plan, PASS_ROWS, bufs, opts, stream,
+        return run_pass(*plan, PASS_ROWS, cap, bufs, opts, stream,
                         [&](void* s) { return enqueue_solve(*plan, w, d, e, lambda, s); });
     }
     if (!ckpt_bytes) {
         Bufs bufs{d, e, lambda, ws, nullptr, nullptr, nullptr, nullptr};
-        return run_pass(*plan, PASS_SOLVE, bufs, opts, stream,
+        return run_pass(*plan, PASS_SOLVE, cap, bufs, opts, stream,
                         [&](void* s) { return enqueue_solve(*plan, w, d, e, lambda, s); });
     }
     Ckpt ck{};
     ckpt_layout(ntot, (int)plan->levels.size(), (char*)ckpt, &ck);
     Bufs bufs{d, e, lambda, ws, ckpt, nullptr, nullptr, nullptr};
-    return run_pass(*plan, PASS_CKPT, bufs, opts, stream,
+    return run_pass(*plan, PASS_CKPT, cap, bufs, opts, stream,
                     [&](void* s) { return enqueue_solve(*plan, w, d, e, lambda, s, &ck); });
 }
 
@@ -367,7 +369,7 @@ int backward(const double* d, const double* e, const std::vector<long long>& off
     Ckpt ck{};
     ckpt_layout(ntot, (int)plan->levels.size(), (char*)const_cast<void*>(ckpt), &ck);
     Bufs bufs{d, e, gin, ckpt, gd, ge, ws, nullptr};
-    return run_pass(*plan, PASS_BACKWARD, bufs, opts, stream,
+    return run_pass(*plan, PASS_BACKWARD, 0, bufs, opts, stream,
                     [&](void* s) { return enqueue_backward(*plan, w, gr, ck, d, e, gin, gd, ge, s); });
 }
 
@@ -725,7 +727,7 @@ int tde_dense_eigvals(double* A, int64_t n, int64_t lda, double* lambda, double*
         const int rc = tde::get_plan(opts, offs, &plan);
         if (rc != TDE_OK) return rc;
         const tde::Bufs bufs{A, ws, (const void*)(intptr_t)lda, nullptr, nullptr, nullptr, nullptr, nullptr};
-        const int rr = tde::run_pass(*plan, tde::PASS_DENSE, bufs, opts, hip_stream, [&](void* s) {
+        const int rr = tde::run_pass(*plan, tde::PASS_DENSE, 0, bufs, opts, hip_stream, [&](void* s) {
             return tde::enqueue_dense_reduce(A, lda, (int)n, dw, s);
         });
         if (rr != TDE_OK) return rr;
