@@ -455,58 +455,79 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
     int copies = selrows_copies(n, (long long)uniq.size());
     while (copies > 1 && ws_bytes < selrows_layout(n, m, H, copies, nullptr, nullptr)) --copies;
     if (ws_bytes < selrows_layout(n, m, H, copies, nullptr, nullptr)) return TDE_EINVAL;
+    // The passes, their plans and tables before anything is enqueued: whatever
+    // cannot be allocated leaves nothing running.
+    struct Pass {
+        size_t u;  // first distinct row
+        int c;     // copies
+        const Plan* plan;
+        std::vector<long long> rows;  // row of each copy's two channels, -1: none
+    };
+    std::vector<Pass> passes;
+    for (size_t u = 0; u < uniq.size(); u += 2 * (size_t)copies) {
+        Pass ps{u, (int)std::min((uniq.size() - u + 1) / 2, (size_t)copies), nullptr, {}};
+        if (!passes.empty() && passes.back().c == ps.c) {
+            ps.plan = passes.back().plan;
+        } else {
+            Plan* px = nullptr;
+            std::vector<long long> offs;
+            for (int p = 0; p <= ps.c; ++p) offs.push_back(p * n);
+            rc = get_plan(&o, offs, &px);
+            if (rc != TDE_OK) return rc;
+            if ((int)px->levels.size() > H) return TDE_EINVAL;
+            ps.plan = px;
+        }
+        ps.rows.assign((size_t)(2 * ps.c), -1);
+        for (size_t k = 0; k < ps.rows.size() && u + k < uniq.size(); ++k) ps.rows[k] = uniq[u + k];
+        passes.push_back(std::move(ps));
+    }
     SelLayout sl{};
     selrows_layout(n, m, H, copies, (char*)ws, &sl);
-    Work w{};
-    workspace_layout(n, 1, n, (char*)ws, &w);
-    w.sec_cap = cap;
-    // pass 0: eigenvalues, checkpoint, unsigned top rows 0 and n-1
-    w.rows_out = 1;
-    w.rows_raw = 1;
-    w.qfirst = sl.q0;
-    w.qlast = sl.q1;
-    if (enqueue_solve(*plan, w, d, e, lambda, stream, &sl.ck) != 0) return TDE_EDEVICE;
-    if (m == 0) return TDE_OK;
     const hipStream_t s = (hipStream_t)stream;
-    if (hipMemcpyAsync(sl.slot, slot.data(), sizeof(int) * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess)
-        return TDE_EDEVICE;
-    std::vector<std::vector<long long>> pass_rows;  // outlive their copies (the stream is waited for below)
-    for (size_t u = 0; u < uniq.size(); u += 2 * (size_t)copies) {
-        const int c = (int)std::min((uniq.size() - u + 1) / 2, (size_t)copies);
-        // the pass's plan: c copies of the problem
-        Plan* px = nullptr;
-        std::vector<long long> offs;
-        for (int p = 0; p <= c; ++p) offs.push_back(p * n);
-        rc = get_plan(&o, offs, &px);
-        if (rc != TDE_OK) return rc;
-        if ((int)px->levels.size() > H) return TDE_EINVAL;
-        std::vector<long long> r((size_t)(2 * c), -1);
-        for (size_t k = 0; k < r.size() && u + k < uniq.size(); ++k) r[k] = uniq[u + k];
-        pass_rows.push_back(std::move(r));
-        if (hipMemcpyAsync(sl.rows, pass_rows.back().data(), 8 * 2 * (size_t)c, hipMemcpyHostToDevice, s) != hipSuccess)
-            return TDE_EDEVICE;
-        const double *dx = d, *ex = e;
-        if (c > 1) {
-            if (enqueue_selrows_copies(d, e, n, c, sl.dr, sl.er, stream) != 0) return TDE_EDEVICE;
-            dx = sl.dr;
-            ex = sl.er;
+    auto enqueue = [&]() -> bool {
+        // pass 0: eigenvalues, checkpoint, unsigned top rows 0 and n-1
+        Work w{};
+        workspace_layout(n, 1, n, (char*)ws, &w);
+        w.sec_cap = cap;
+        w.rows_out = 1;
+        w.rows_raw = 1;
+        w.qfirst = sl.q0;
+        w.qlast = sl.q1;
+        if (enqueue_solve(*plan, w, d, e, lambda, stream, &sl.ck) != 0) return false;
+        if (m > 0 &&
+            hipMemcpyAsync(sl.slot, slot.data(), sizeof(int) * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess)
+            return false;
+        for (const Pass& ps : passes) {
+            const int c = ps.c;
+            if (hipMemcpyAsync(sl.rows, ps.rows.data(), 8 * ps.rows.size(), hipMemcpyHostToDevice, s) != hipSuccess)
+                return false;
+            const double *dx = d, *ex = e;
+            if (c > 1) {
+                if (enqueue_selrows_copies(d, e, n, c, sl.dr, sl.er, stream) != 0) return false;
+                dx = sl.dr;
+                ex = sl.er;
+            }
+            Work wx{};
+            workspace_layout(c * n, c, c * n, (char*)ws, &wx);
+            wx.sec_cap = cap;
+            wx.rows_out = 1;
+            wx.xmode = 1;
+            wx.xn = n;
+            wx.xrows = sl.rows;
+            wx.xa = sl.xa;
+            wx.xb = sl.xb;
+            if (enqueue_solve(*ps.plan, wx, dx, ex, lambda, stream, nullptr, &sl.ck) != 0) return false;
+            if (enqueue_selrows_out(Q, m, n, sl.slot, (int)ps.u, c, sl.xa, sl.xb, sl.q0, sl.q1, stream) != 0)
+                return false;
         }
-        Work wx{};
-        workspace_layout(c * n, c, c * n, (char*)ws, &wx);
-        wx.sec_cap = cap;
-        wx.rows_out = 1;
-        wx.xmode = 1;
-        wx.xn = n;
-        wx.xrows = sl.rows;
-        wx.xa = sl.xa;
-        wx.xb = sl.xb;
-        if (enqueue_solve(*px, wx, dx, ex, lambda, stream, nullptr, &sl.ck) != 0) return TDE_EDEVICE;
-        if (enqueue_selrows_out(Q, m, n, sl.slot, (int)u, c, sl.xa, sl.xb, sl.q0, sl.q1, stream) != 0)
-            return TDE_EDEVICE;
-    }
-    // the host tables must outlive their copies (pageable memory)
+        return true;
+    };
+    const bool ok = enqueue();
+    if (ok && m == 0) return TDE_OK;
+    // the host tables must outlive their copies (pageable memory), also where
+    // a later step could not be enqueued
     if (hipStreamSynchronize(s) != hipSuccess) return TDE_EDEVICE;
-    return TDE_OK;
+    return ok ? TDE_OK : TDE_EDEVICE;
 }
 
 // Driver pre-pass: pairwise merge schedule of the blocks of every problem
