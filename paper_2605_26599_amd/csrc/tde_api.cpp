@@ -10,6 +10,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <tuple>
 #include <vector>
 
@@ -377,12 +378,12 @@ int backward(const double* d, const double* e, const std::vector<long long>& off
 // workspace of the passes (each solves `copies` copies of the problem side by
 // side, two rows in each) starts with the forward's; beyond it lie a forward
 // checkpoint, the rows the passes carry, the unsigned top rows 0 and n-1, the
-// copies' matrix, their row numbers and the requests' distinct rows.
+// copies' matrix, their row numbers and the requests in order of their rows.
 struct SelLayout {
     Ckpt ck;
     double *xa, *xb, *q0, *q1, *dr, *er;
     long long* rows;
-    int* slot;
+    int* order;
 };
 
 size_t selrows_layout(long long n, long long m, int levels, int copies, char* base, SelLayout* L) {
@@ -406,7 +407,7 @@ size_t selrows_layout(long long n, long long m, int levels, int copies, char* ba
         t.dr = (double*)take(8 * nn * (size_t)c);
         t.er = (double*)take(8 * nn * (size_t)c);
     }
-    t.slot = (int*)take(4 * (size_t)(m > 0 ? m : 1));
+    t.order = (int*)take(4 * (size_t)(m > 0 ? m : 1));
     if (L) *L = t;
     return off;
 }
@@ -417,7 +418,7 @@ size_t selrows_layout(long long n, long long m, int levels, int copies, char* ba
 // of 0.7 ms), and the workspace stays near 300 bytes times 2^18 columns.
 int selrows_copies(long long n, long long m) {
     long long c = (m + 1) / 2;
-    c = std::min(c, std::min(8LL, (1LL << 18) / std::max(n, 1LL)));
+    c = std::min(c, std::min((long long)kSelCopies, (1LL << 18) / std::max(n, 1LL)));
     return (int)std::max(c, 1LL);
 }
 
@@ -441,16 +442,18 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
     if (rc != TDE_OK) return rc;
     const int H = tree_levels(leaf, {0, n});
     if ((int)plan->levels.size() > H) return TDE_EINVAL;
-    // distinct rows, ascending, and the one each request wants
-    std::map<long long, int> distinct;
-    for (long long i = 0; i < m; ++i) distinct.emplace(rows[i], 0);
+    // distinct rows, ascending, each with its requests order[first..)
+    std::vector<int> order((size_t)m);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return rows[a] < rows[b]; });
     std::vector<long long> uniq;
-    for (auto& u : distinct) {
-        u.second = (int)uniq.size();
-        uniq.push_back(u.first);
+    std::vector<int> first;
+    for (size_t i = 0; i < order.size(); ++i) {
+        if (i > 0 && rows[order[i]] == uniq.back()) continue;
+        uniq.push_back(rows[order[i]]);
+        first.push_back((int)i);
     }
-    std::vector<int> slot((size_t)m);
-    for (long long i = 0; i < m; ++i) slot[(size_t)i] = distinct[rows[i]];
+    first.push_back((int)m);
     // as many copies per pass as the rows need and the workspace holds
     int copies = selrows_copies(n, (long long)uniq.size());
     while (copies > 1 && ws_bytes < selrows_layout(n, m, H, copies, nullptr, nullptr)) --copies;
@@ -458,14 +461,14 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
     // The passes, their plans and tables before anything is enqueued: whatever
     // cannot be allocated leaves nothing running.
     struct Pass {
-        size_t u;  // first distinct row
-        int c;     // copies
+        int c;  // copies
         const Plan* plan;
         std::vector<long long> rows;  // row of each copy's two channels, -1: none
+        SelRequests req;
     };
     std::vector<Pass> passes;
     for (size_t u = 0; u < uniq.size(); u += 2 * (size_t)copies) {
-        Pass ps{u, (int)std::min((uniq.size() - u + 1) / 2, (size_t)copies), nullptr, {}};
+        Pass ps{(int)std::min((uniq.size() - u + 1) / 2, (size_t)copies), nullptr, {}, {}};
         if (!passes.empty() && passes.back().c == ps.c) {
             ps.plan = passes.back().plan;
         } else {
@@ -479,6 +482,7 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
         }
         ps.rows.assign((size_t)(2 * ps.c), -1);
         for (size_t k = 0; k < ps.rows.size() && u + k < uniq.size(); ++k) ps.rows[k] = uniq[u + k];
+        for (size_t k = 0; k <= ps.rows.size(); ++k) ps.req.first[k] = first[std::min(u + k, uniq.size())];
         passes.push_back(std::move(ps));
     }
     SelLayout sl{};
@@ -495,7 +499,7 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
         w.qlast = sl.q1;
         if (enqueue_solve(*plan, w, d, e, lambda, stream, &sl.ck) != 0) return false;
         if (m > 0 &&
-            hipMemcpyAsync(sl.slot, slot.data(), sizeof(int) * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess)
+            hipMemcpyAsync(sl.order, order.data(), sizeof(int) * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess)
             return false;
         for (const Pass& ps : passes) {
             const int c = ps.c;
@@ -517,7 +521,7 @@ int selrows(const double* d, const double* e, long long n, const int64_t* rows, 
             wx.xa = sl.xa;
             wx.xb = sl.xb;
             if (enqueue_solve(*ps.plan, wx, dx, ex, lambda, stream, nullptr, &sl.ck) != 0) return false;
-            if (enqueue_selrows_out(Q, m, n, sl.slot, (int)ps.u, c, sl.xa, sl.xb, sl.q0, sl.q1, stream) != 0)
+            if (enqueue_selrows_out(Q, n, sl.order, ps.req, c, sl.xa, sl.xb, sl.q0, sl.q1, stream) != 0)
                 return false;
         }
         return true;

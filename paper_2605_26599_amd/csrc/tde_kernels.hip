@@ -3148,21 +3148,23 @@ __global__ __launch_bounds__(kWG) void k_bwd_edges(const long long* __restrict__
 // Requested rows: the rows of one pass to their places in Q [m][n], every
 // eigenvector column signed like the boundary rows (the first entry >= 0, the
 // last when the first is 0; q0 / q1 are the unsigned top rows of the same
-// solve).  Request i wants distinct row slot[i]; the pass holds the slots
-// [u0, u0 + 2 copies), slot u0 + 2p + c in channel c of copy p.  One thread
-// per column.
-__global__ __launch_bounds__(kWG) void k_selrows_out(double* __restrict__ Q, long long m, long long n,
-                                                     const int* __restrict__ slot, int u0, int copies,
+// solve).  The requests come sorted by row, so a pass visits its own alone and
+// the passes together write every request once (a walk over all requests in
+// every pass took 0.22 s of 0.54 s for all 8192 rows of n = 8192; now bound by
+// the writes, 0.32 s in all).  One thread per column.
+__global__ __launch_bounds__(kWG) void k_selrows_out(double* __restrict__ Q, long long n,
+                                                     const int* __restrict__ order, SelRequests req, int copies,
                                                      const double* __restrict__ xa, const double* __restrict__ xb,
                                                      const double* __restrict__ q0, const double* __restrict__ q1) {
     const long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (k >= n) return;
     const double a = q0[k], b = q1[k];
     const double sg = (a < 0.0 || (a == 0.0 && b < 0.0)) ? -1.0 : 1.0;
-    for (long long i = 0; i < m; ++i) {
-        const int u = slot[i] - u0;
-        if (u < 0 || u >= 2 * copies) continue;
-        Q[i * n + k] = ((u & 1) ? xb : xa)[(long long)(u >> 1) * n + k] * sg;
+    for (int u = 0; u < 2 * copies; ++u) {
+        const int i0 = req.first[u], i1 = req.first[u + 1];
+        if (i0 == i1) continue;  // a channel without a row
+        const double v = ((u & 1) ? xb : xa)[(long long)(u >> 1) * n + k] * sg;
+        for (int i = i0; i < i1; ++i) Q[order[i] * n + k] = v;
     }
 }
 
@@ -3742,10 +3744,10 @@ __global__ __launch_bounds__(kWG) void k_merge_runs(const MergeRec* __restrict__
     dst[R.off + pos] = x;
 }
 
-int enqueue_selrows_out(double* Q, long long m, long long n, const int* slot, int u0, int copies, const double* xa,
-                        const double* xb, const double* q0, const double* q1, void* stream) {
-    if (m <= 0 || n <= 0) return 0;
-    TDE_LAUNCH_K(KIND_ASSEMBLE, k_selrows_out, nblk(n, kWG), kWG, stream, Q, m, n, slot, u0, copies, xa, xb, q0, q1);
+int enqueue_selrows_out(double* Q, long long n, const int* order, const SelRequests& req, int copies,
+                        const double* xa, const double* xb, const double* q0, const double* q1, void* stream) {
+    if (n <= 0) return 0;
+    TDE_LAUNCH_K(KIND_ASSEMBLE, k_selrows_out, nblk(n, kWG), kWG, stream, Q, n, order, req, copies, xa, xb, q0, q1);
     return (int)hipGetLastError();
 }
 

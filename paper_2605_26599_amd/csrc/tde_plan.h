@@ -88,13 +88,18 @@ int enqueue_solve(const Plan& p, const Work& w, const double* d, const double* e
 // spectra and boundary rows from the checkpoint xsrc of a forward solve of the
 // same inputs and plan instead of the workspace.
 
-// Requested rows: `copies` times (d, e) in the batched layout, and one pass's
-// rows to Q [m][n], signed by the unsigned top rows q0, q1 (first entry >= 0);
-// slot[i] (device): the distinct row that request i wants.
+// Requested rows: `copies` (at most kSelCopies) times (d, e) in the batched
+// layout, and one pass's rows to Q [m][n], signed by the unsigned top rows q0,
+// q1 (first entry >= 0).  The requests order[first[k]..first[k + 1]) (order on
+// the device) want the row that channel k % 2 of copy k / 2 carries.
+constexpr int kSelCopies = 8;
+struct SelRequests {
+    int first[2 * kSelCopies + 1];
+};
 int enqueue_selrows_copies(const double* d, const double* e, long long n, int copies, double* dr, double* er,
                            void* stream);
-int enqueue_selrows_out(double* Q, long long m, long long n, const int* slot, int u0, int copies, const double* xa,
-                        const double* xb, const double* q0, const double* q1, void* stream);
+int enqueue_selrows_out(double* Q, long long n, const int* order, const SelRequests& req, int copies,
+                        const double* xa, const double* xb, const double* q0, const double* q1, void* stream);
 
 // Driver pre-pass: negligible-coupling flags (flags[i] = 1: a block starts at
 // column i), and one pass of pairwise merges of ascending runs (src -> dst).

@@ -1,12 +1,14 @@
 // The host side of a requested-rows call (tde_api.cpp over a HIP runtime on
 // host memory, the kernels' launchers replaced by recorders): an allocation, a
 // copy or a launch that fails at any point leaves nothing running behind a
-// returned call, and an allocation fails before anything was enqueued.
+// returned call, and an allocation fails before anything was enqueued; and the
+// passes' requests are every request once, at the row it asks for.
 #include "fake_hip/hip/hip_runtime.h"
 
 #include <cstdio>
 #include <cstdlib>
 #include <random>
+#include <utility>
 #include <vector>
 
 #include "../../include/tde.h"
@@ -21,15 +23,22 @@ static int launched() {
     return 0;
 }
 
+static std::vector<long long> g_xrows;                  // the rows of the last pass enqueued
+static std::vector<std::pair<int, long long>> g_given;  // (request, row) of every pass
+
 namespace tde {
-int enqueue_solve(const Plan&, const Work&, const double*, const double*, double*, void*, const Ckpt*, const Ckpt*) {
+int enqueue_solve(const Plan& p, const Work& w, const double*, const double*, double*, void*, const Ckpt*,
+                  const Ckpt* xsrc) {
+    if (xsrc) g_xrows = std::vector<long long>(w.xrows, w.xrows + 2 * p.B);
     return launched();
 }
 int enqueue_selrows_copies(const double*, const double*, long long, int, double*, double*, void*) {
     return launched();
 }
-int enqueue_selrows_out(double*, long long, long long, const int*, int, int, const double*, const double*,
-                        const double*, const double*, void*) {
+int enqueue_selrows_out(double*, long long, const int* order, const SelRequests& req, int copies, const double*,
+                        const double*, const double*, const double*, void*) {
+    for (int u = 0; u < 2 * copies; ++u)
+        for (int i = req.first[u]; i < req.first[u + 1]; ++i) g_given.push_back({order[i], g_xrows[u]});
     return launched();
 }
 int enqueue_split_flags(const double*, const double*, long long, int*, void*) { return 0; }
@@ -73,6 +82,7 @@ struct Call {
         tde_release_plans();
         fake::fail_malloc = fake::fail_async = g_fail_launch = -1;
         g_launches = fake::pending = fake::syncs = 0;
+        g_given.clear();
     }
 };
 
@@ -81,6 +91,19 @@ int main() {
     int step = -1;
     c.reset();
     CHECK(c.run() == TDE_OK && fake::pending == 0 && g_launches > 8);
+    for (auto [n, m] : {std::pair<int, int>{1, 1}, {1, 40}, {2, 3}, {16, 16}, {17, 17}, {33, 500}, {300, 16},
+                        {300, 33}, {300, 2000}, {9, 0}}) {
+        Call x(n, m);
+        x.reset();
+        CHECK(x.run() == TDE_OK);
+        std::vector<int> seen((size_t)m, 0);
+        for (auto [i, row] : g_given) {
+            CHECK(i >= 0 && i < m && row == x.rows[(size_t)i]);
+            if (i >= 0 && i < m) ++seen[(size_t)i];
+        }
+        for (int k : seen) CHECK(k == 1);
+        step = n;
+    }
     for (int kind = 0; kind < 3; ++kind) {
         int failed = 0;
         for (step = 0; step < 200; ++step) {

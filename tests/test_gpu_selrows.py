@@ -185,3 +185,23 @@ def test_selrows_shared_passes(tde, n, m):
     assert L.tde_get_status(ws.data_ptr(), stream) == tde.TDE_OK
     assert np.array_equal(lam, lam2.cpu().numpy()) and np.array_equal(Q, Q2.cpu().numpy())
     assert L.tde_eigvals_selrows(*args, nb - 4 * m - 256, stream, None) == tde.TDE_EINVAL
+
+
+@pytest.mark.parametrize("n,m", [(1500, 1700), (40, 3000)])
+def test_selrows_many_requests(tde, n, m):
+    """Every row and repeats of some, in any order: many passes, each giving its
+    own requests alone.  The rows are those of one orthogonal matrix (levels
+    deflate up to 8 eps each and rounding adds up over eleven of them: 1e-12)."""
+    g = np.random.default_rng(m)
+    d, e = tdgen.tridiag("normal", n, cfg=tdgen.CFG_TEST)
+    rows = np.concatenate([g.permutation(n), g.integers(0, n, m - n)])
+    g.shuffle(rows)
+    _step(f"selrows many requests n={n} m={m}")
+    lam, Q = _sel(tde, d, e, [int(r) for r in rows])
+    assert np.isfinite(Q).all()
+    full = np.empty((n, n))
+    full[rows] = Q
+    assert np.array_equal(full[rows], Q)  # repeats are copies
+    assert np.abs(full @ full.T - np.eye(n)).max() <= 1e-12
+    T = np.diag(d) + np.diag(e, 1) + np.diag(e, -1)
+    assert np.abs(full @ np.diag(lam) @ full.T - T).max() <= 1e-12 * tdgen.tnorm1(d, e)
