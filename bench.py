@@ -84,7 +84,7 @@ def source_hash():
     launch code): hardware-counter figures stay valid while it is unchanged."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2605_26599_amd", "csrc")
-    for f in ("tde_internal.h", "tde_device.h", "tde_adjoint.h"):
+    for f in ("tde_internal.h", "tde_device.h", "tde_adjoint.h", "tde_far.h"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     with open(os.path.join(csrc, "tde_kernels.hip"), "rb") as fh:

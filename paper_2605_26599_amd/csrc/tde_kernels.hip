@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "tde_adjoint.h"
+#include "tde_far.h"
 #include "tde_plan.h"
 
 #include <mutex>
@@ -977,8 +978,8 @@ __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b,
 // lie in one short interval [c - h, c + h] of the spectrum, and over it the
 // contribution of every pole with |D_j - c| >= kFarRatio h is smooth: with
 // u = h/(D_j - c) and t = (x - c)/h, 1/(D_j - x) = (u/h) sum_k u^k t^k with
-// |u| <= 1/kFarRatio and |t| <= 1, and kFarTerms terms leave less than
-// 2 * 4^-28 = 3e-17 of it.  So a block sums the moments of its far poles once
+// |u| <= 1/kFarRatio and |t| <= 1 (tde_far.h: the sums and what kFarTerms terms
+// leave of them).  So a block sums the moments of its far poles once
 // (one pole per thread, two fused operations per moment) and every later
 // sweep visits only the near poles and evaluates a polynomial: the O(K) cost
 // per root and sweep becomes O(K) per block plus the near window (about four
@@ -991,21 +992,15 @@ __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b,
 //
 // kFarRatio and kFarTerms: a far pole costs 37 operations and its reciprocal
 // per block, a near one about 13 per pole, root and sweep; ratio 4 with 28
-// terms balances the two at K of a few ten thousand.  Poles with |u| <= 1/12
-// leave as little after 16 terms and those with |u| <= 1/128 after 8, so most
-// of a large merge's poles (consecutive ones, 64 to a wave, so nearly every
-// wave agrees) stop there.
+// terms balances the two at K of a few ten thousand.  Distant poles stop after
+// 16 or 8 terms: consecutive ones, 64 to a wave, so nearly every wave agrees.
 // Measured (Toeplitz n = 65536, seven wide levels, K up to 65536): sweeps over
 // all poles were FP64-issue-bound at 33% of the peak, 13.7 ms the solve; with
 // 28 terms (56 operations) for every far pole secular 0.64, Loewner 0.45, rows
 // 0.61 and 2.41 ms; with shorter sums 0.57, 0.40, 0.47 and 2.15 ms, at 14 to 19%
-// of the peak, bound by load latency at two workgroups per compute unit.  The solve's largest error is unchanged (5e-16 of the spectrum's
-// norm or less).
+// of the peak, bound by load latency at two workgroups per compute unit.  The
+// solve's largest error is unchanged (5e-16 of the spectrum's norm or less).
 // ---------------------------------------------------------------------------
-constexpr int kFarTerms = 28;
-constexpr int kFarFold = 32;  // kFarTerms padded to the fold's power of two
-constexpr double kFarRatio = 4.0;
-constexpr double kFarHalf = 1.0 / 12.0, kFarShort = 1.0 / 128.0;
 constexpr int kFarMin = 192;
 // LDS of the expansions: NW folded partials and two coefficient sets.
 constexpr int far_lds(int nw) { return (nw + 2) * kFarFold; }
@@ -1077,65 +1072,10 @@ __device__ __forceinline__ double wave_fold(double (&m)[kFarFold]) {
     return m[0] + __shfl_xor(m[0], 1, 64);
 }
 
-// Adds v u^k to m[k] for the k that count: four moments per step of u^4 (37
-// operations for 28 moments instead of the 56 of taking each power from the
-// last one), 8 or 16 moments where every lane's u is small enough.
-__device__ __forceinline__ void far_add(double (&m)[kFarFold], double v, double u) {
-    const double au = fabs(u);
-    const double u2 = u * u, u3 = u2 * u, u4 = u2 * u2;
-    auto four = [&](int k) {
-        m[k] += v;
-        m[k + 1] = fma(v, u, m[k + 1]);
-        m[k + 2] = fma(v, u2, m[k + 2]);
-        m[k + 3] = fma(v, u3, m[k + 3]);
-        v *= u4;
-    };
-    four(0);
-    four(4);
-    if (__any(au > kFarShort)) {
-        four(8);
-        four(12);
-        if (__any(au > kFarHalf)) {
-            four(16);
-            four(20);
-            four(24);
-        }
-    }
-}
-// Adds u^(k+1) - v^(k+1) to m[k], du = u - v, by
-// u^(k+j) - v^(k+j) = u^j (u^k - v^k) + v^k (u^j - v^j).
-__device__ __forceinline__ void far_add_log(double (&m)[kFarFold], double u, double v, double du) {
-    const double au = fmax(fabs(u), fabs(v));
-    const double u2 = u * u, v2 = v * v, u3 = u2 * u, u4 = u2 * u2, v4 = v2 * v2;
-    const double d2 = du * (u + v), d3 = fma(u, d2, v2 * du), d4 = d2 * (u2 + v2);
-    double em = du;  // u^(k+1) - v^(k+1)
-    double vm = v;   // v^(k+1)
-    auto four = [&](int k) {
-        m[k] += em;
-        m[k + 1] = fma(u, em, fma(vm, du, m[k + 1]));
-        m[k + 2] = fma(u2, em, fma(vm, d2, m[k + 2]));
-        m[k + 3] = fma(u3, em, fma(vm, d3, m[k + 3]));
-        em = fma(u4, em, vm * d4);
-        vm *= v4;
-    };
-    four(0);
-    four(4);
-    if (__any(au > kFarShort)) {
-        four(8);
-        four(12);
-        if (__any(au > kFarHalf)) {
-            four(16);
-            four(20);
-            four(24);
-        }
-    }
-}
-static_assert(kFarTerms == 28, "far_add and far_add_log write the steps out");
-
 // Moments over the workgroup: term(j, v, u) gives pole j's first moment v and
-// its ratio u (moment k is the sum of v u^k); j runs over [0, n0) and [n1, K)
-// when both is set, else over [j0, j1) alone.  The kFarTerms totals land in
-// coef (LDS) after the closing barrier.  part: NW x kFarFold doubles of LDS.
+// its ratio u (moment k is the sum of v u^k); j runs over [j0, j1) and
+// [j2, j3).  The kFarTerms totals land in coef (LDS) after the closing barrier.
+// part: NW x kFarFold doubles of LDS.
 template <int NW, class Term>
 __device__ __forceinline__ void far_moments(int j0, int j1, int j2, int j3, double* part, double* coef, Term term) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1158,27 +1098,6 @@ __device__ __forceinline__ void far_moments(int j0, int j1, int j2, int j3, doub
         coef[threadIdx.x] = x;
     }
     __syncthreads();
-}
-
-// The polynomial sum_k coef[k] t^k, and with its first derivative by t and half
-// its second one.
-__device__ __forceinline__ double far_value(const double* coef, double t) {
-    double s = coef[kFarTerms - 1];
-#pragma unroll
-    for (int k = kFarTerms - 2; k >= 0; --k) s = fma(s, t, coef[k]);
-    return s;
-}
-__device__ __forceinline__ double far_value(const double* coef, double t, double* d1, double* d2) {
-    double s = coef[kFarTerms - 1], d = 0.0, c = 0.0;
-#pragma unroll
-    for (int k = kFarTerms - 2; k >= 0; --k) {
-        c = fma(c, t, d);
-        d = fma(d, t, s);
-        s = fma(s, t, coef[k]);
-    }
-    *d1 = d;
-    *d2 = c;
-    return s;
 }
 
 // Workgroup total (every thread gets the same bits); red: NW doubles of LDS,
