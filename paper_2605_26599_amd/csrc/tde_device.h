@@ -959,17 +959,6 @@ TDE_DEV void body_runs(long long g, int m, const MergeRec* __restrict__ mr, cons
     runs_from(g, gs, ge, merge_tol(w.D, R.pk, s), v, on_rotate);
 }
 
-// Largest m with scan[mr[m].pk] <= g: the merge owning active column g.
-TDE_DEV int find_merge_active(const MergeRec* __restrict__ mr, int M, const int* __restrict__ scan, long long g) {
-    int lo = 0, hi = M - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (scan[mr[mid].pk] <= g) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // Root-parallel steps.  m is the merge owning active column g (recorded at
 // compaction).  The merge's active arrays are read through views: element
 // ks + j of the level-wide array is view[ks + j - voff], so a caller can pass

@@ -120,18 +120,17 @@ struct Work {
     double* RL2;               // [n]
     double* RH2;               // [n]
     int* st;                   // [n]   column state: 0 negligible z, 1 active, 2 rotated away
-    int* scan;                 // [n + n/2 + 2] exclusive prefix counts of active columns (level-wide, or per merge)
-    int* scanC;                // [n + n/2 + 2] the same for candidate (non-negligible) columns
-    int* scanR;                // [n + n/2 + 2] the same for rotated-away columns
+    int* scan;                 // [n+1] level-wide exclusive prefix counts of active columns
+    int* scanC;                // [n+1] the same for candidate (non-negligible) columns
+    int* scanR;                // [n+1] the same for rotated-away columns
     int* bsum;                 // [nb+1] per-block counts
     int* bsumR;                // [nb+1] per-block counts of rotated-away columns (this level's slice of bcnt)
     int* bsumA;                // [nb+1] per-block counts of active columns (raw; this level's slice of bcnt)
     int* bcnt;                 // [kMaxLevels][2][nb+2] per-level block counts, zeroed once per pass
     int* bsumAs;               // [nb+1] exclusive scan of bsumA
     int* bsumRs;               // [nb+1] exclusive scan of bsumR
-    unsigned* ticket;          // [1]   last-workgroup ticket (self-resetting)
     int* nnpos;                // [n]   packed positions of non-negligible columns
-    int* cf;                   // [n]   close-pair flag of non-negligible column g and g+1
+    int* cf;                   // [n]   spare
     double* Da;                // [n]   active poles
     double* Za;                // [n]   active z
     double* Wa;                // [n]   active z^2 (the weights the wide secular sweep reads)

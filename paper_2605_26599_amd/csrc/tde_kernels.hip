@@ -2282,7 +2282,6 @@ struct SmallStageT {
     double D[CAP], W[CAP], Z[CAP], T[CAP], H[CAP], L[CAP], R[CAP];
     int O[CAP];
 };
-using SmallStage = SmallStageT<kFuseMax>;
 
 // Roots, Loewner z and rows of one merge with 1 <= K <= CAP active columns at
 // active index ks (the whole workgroup; block-uniform arguments).  gmax caps

@@ -104,7 +104,6 @@ size_t workspace_layout(long long n, long long B, long long maxM, char* base, Wo
     const long long nb = (nn + kWG - 1) / kWG + 2;
     Work t{};
     t.status = (int*)take(kCntOffset);
-    t.ticket = t.status ? (unsigned*)((char*)t.status + 16) : nullptr;
     t.counters = (unsigned long long*)take(sizeof(unsigned long long) * CNT_N * kCntSlots);
     t.pmax = (unsigned long long*)take(sizeof(unsigned long long) * (B > 0 ? B : 1));
     t.lam = (double*)take(8 * nn);
@@ -120,8 +119,8 @@ size_t workspace_layout(long long n, long long B, long long maxM, char* base, Wo
     t.RL2 = (double*)take(8 * nn);
     t.RH2 = (double*)take(8 * nn);
     t.st = (int*)take(4 * nn);
-    // prefix arrays: n + 1 entries for the level-wide scans, plus one per merge
-    // (at most n/2 + 1) for k_level_block's merge-local counts
+    // prefix arrays: n + 1 entries for the level-wide scans (the carving keeps
+    // room for one more per merge)
     t.scan = (int*)take(4 * (nn + nn / 2 + 2));
     t.scanC = (int*)take(4 * (nn + nn / 2 + 2));
     t.scanR = (int*)take(4 * (nn + nn / 2 + 2));
