@@ -207,15 +207,19 @@ int tde_eigvals_selrows(const double* d, const double* e, int64_t n, const int64
  * matrix cores) and solves T by boundary-row divide and conquer.
  *   A      [lda*n]  device, column-major, the whole symmetric matrix (both
  *                   triangles, which must agree); destroyed: the reduction
- *                   updates its trailing blocks in place
+ *                   updates its trailing blocks in place.  The squares of its
+ *                   entries must be in range: the reduction does not scale
  *   lda    >= n
  *   lambda [n]      output eigenvalues of A, ascending (device)
  *   d_out  [n], e_out [n-1]  device, may be NULL: the diagonal and subdiagonal of T
  *   ws     ws_bytes >= tde_dense_workspace_bytes(n, opts) (device): the
  *                   solver's workspace (first, so tde_get_status(ws) reads its
- *                   status), then about 133 n doubles of reduction scratch
+ *                   status), then reduction scratch: about (69 + t) n
+ *                   doubles for t tiles a side, t <= 64 up to n = 65536 (133 n
+ *                   there) and n / 1024 beyond
  * Asynchronous on the stream; the reduction's kernels (two per column, two
- * per panel) are replayed as a graph like a solve's.  Returns TDE_OK or a negative code.
+ * per panel) are replayed as a graph like a solve's.  Returns TDE_OK or a
+ * negative code.
  * tde_dense_workspace_bytes returns 0 on a bad argument. */
 size_t tde_dense_workspace_bytes(int64_t n, const tde_opts* opts);
 int tde_dense_eigvals(double* A, int64_t n, int64_t lda, double* lambda, double* d_out, double* e_out, void* ws,

@@ -157,6 +157,11 @@ TDE_DEV void bwd_root_coeffs(int K, const double* __restrict__ D, const double* 
 //   dL/dA_pi (sym) = z_i sum_b X_p(b) a_pb a_ib / N_b   (secular column i)
 // and for the negligible z_p, summed against rho z_i over all i,
 //   dL/dz_p = -sum_b X_p(b) a_pb / N_b.
+// A root lambda_b equal to D_p makes one eigenspace of the two columns, whose
+// basis is free and which the loss cannot depend on: it contributes nothing.
+// (d = (0, 0, 1, 0, 1), e = (1, 1, 1, 0) in leaves of two meets one: its last
+// three columns have the roots -1, 1 and the deflated pole 1, though the whole
+// matrix has five distinct eigenvalues.)
 // S receives sum_b {blo_b, bhi_b, gblo_b, gbhi_b}/N_b * a_pb * (a_ib or 1).
 template <class Red>
 TDE_DEV void bwd_defl_sums(int K, const double* __restrict__ D, const int* __restrict__ org,
@@ -170,7 +175,8 @@ TDE_DEV void bwd_defl_sums(int K, const double* __restrict__ D, const int* __res
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     for (int b = sub; b < K; b += G) {
         const double Do = D[org[b]];
-        double k = rcp_nr((Dp - Do) - tau[b]);
+        const double dp = (Dp - Do) - tau[b];
+        double k = (dp != 0.0) ? rcp_nr(dp) : 0.0;  // a root at the deflated pole itself: see above
         if (i >= 0) k *= rcp_nr((Di - Do) - tau[b]);
         s0 += bl[b] * k;
         s1 += bh[b] * k;

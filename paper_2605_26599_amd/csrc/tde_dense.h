@@ -9,11 +9,11 @@ constexpr int kNb = 32;  // panel width (reflectors per trailing update)
 
 // Scratch of one reduction of an n x n matrix: the panel's reflectors V and
 // the matching W (n x kNb each, column-major, global row index), the tiles'
-// products with v (ypart, one row per tile, at most 64) and their shares of
-// v^T A22 v (ydot), the panel's tau, the column's dot products W^T v and V^T v
-// (sdot), the next reflector unscaled (ua), its norm and its products with W
-// and V as partial sums per 64 rows (partN, partD), and the tridiagonal's
-// d[n], e[n].
+// products with v (ypart, one row per tile side: at most 64 up to n = 65536,
+// n / 1024 beyond) and their shares of v^T A22 v (ydot), the panel's tau, the
+// column's dot products W^T v and V^T v (sdot), the next reflector unscaled
+// (ua), its norm and its products with W and V as partial sums per 64 rows
+// (partN, partD), and the tridiagonal's d[n], e[n].
 struct DenseWork {
     double* V;
     double* W;

@@ -12,9 +12,8 @@
 // alpha = -tau/2 (w^T v) is taken against the trailing matrix as it stood at
 // the start of the panel; after the panel the trailing matrix receives the
 // rank-2b update A22 <- A22 - V W^T - W V^T as one matrix product on the FP64
-// matrix cores.  A is kept in full (both triangles), so the per-column
-// product A22 v reads whole columns (contiguous in memory, column-major):
-// y_r = A[:, r] . v, one wave per column r.
+// matrix cores.  Only the T x T tiles of the lower triangle are read and kept up
+// to date (the diagonal ones in full); what lies above them goes stale.
 //
 // Per column two launches, each spread over the whole chip:
 //   k_trd_sym: tau and scale of the column's reflector (every wave sums the
@@ -29,7 +28,8 @@
 // Per panel k_trd_row for its first column and after its last one, and
 // k_trd_syr2k on the lower triangle's tiles.
 // The traffic is the lower triangle read once per column, 4 n^3 / 3 bytes in
-// all, plus about 64 partials per row and column.
+// all, plus one partial per tile side (at most 64 up to n = 65536), row and
+// column.
 #include <hip/hip_runtime.h>
 
 #include "tde_dense.h"
@@ -459,7 +459,8 @@ __global__ void k_trd_tail(const double* __restrict__ A, long long lda, int n, d
 }
 
 // Side of the tiles of k_trd_sym in subtiles: at most 64 tiles a side (so at
-// most 64 partials per row) up to 65536 rows.
+// most 64 partials per row) up to 65536 rows; beyond, tiles of 1024 (their LDS
+// is 40 KB then), n / 1024 a side.
 int dense_sub(long long n) {
     const long long s = (n + 64 * kRows - 1) / (64 * kRows);
     return (int)(s < 1 ? 1 : (s > 16 ? 16 : s));

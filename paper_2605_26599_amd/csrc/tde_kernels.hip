@@ -994,6 +994,9 @@ __device__ __forceinline__ void wide_sweep(cdouble* D, cdouble* W, int a, int b,
 // per block, a near one about 13 per pole, root and sweep; ratio 4 with 28
 // terms balances the two at K of a few ten thousand.  Distant poles stop after
 // 16 or 8 terms: consecutive ones, 64 to a wave, so nearly every wave agrees.
+// kFarMin, with 64, 192 and 768 (Toeplitz): n = 4096 0.78, 0.78, 0.79 ms, n =
+// 16384 1.02, 1.02, 1.05, n = 65536 2.03, 2.03, 2.04, n = 262144 9.8, 9.8, 9.9; a
+// Jacobi matrix of n = 20000 1.40 with each.
 // Measured (Toeplitz n = 65536, seven wide levels, K up to 65536): sweeps over
 // all poles were FP64-issue-bound at 33% of the peak, 13.7 ms the solve; with
 // 28 terms (56 operations) for every far pole secular 0.64, Loewner 0.45, rows
@@ -1810,7 +1813,11 @@ __global__ __launch_bounds__(NW * 64) void k_secular_wide(const MergeRec* __rest
 // The same for the Loewner step and the rows (forward pass).
 // (four waves per SIMD: beyond 128 registers only one workgroup of eight waves
 // would fit a compute unit; the 18 registers spilt cost less than the idle
-// half.  Toeplitz n = 65536: 400 -> 332 us per solve)
+// half where a launch has blocks enough for both: Toeplitz n = 65536 400 -> 332
+// us per solve, the whole solve 2.10 -> 2.03 ms, n = 262144 10.6 -> 9.8 ms.
+// Below about 256 blocks there is no second half to fill and the spills alone
+// remain: n = 16384 1.012 -> 1.021 ms, n = 4096 and a Jacobi matrix of n = 20000
+// without a difference)
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_lowner_wide(
     const MergeRec* __restrict__ mr, int M, const double* __restrict__ e, const unsigned long long* __restrict__ pmax,
