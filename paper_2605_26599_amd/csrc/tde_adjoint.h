@@ -19,7 +19,8 @@
 //   Q (diag(gl) + B) Q^T,  B_jk = (q_0j gblo_k + q_{l-1,j} gbhi_k)/(l_k - l_j), j != k,
 // and the tear edits d' = d - |beta| send -sign(beta) dL/dd' to each coupling.
 // The derivatives are those of the computed (deflated) map, which is the
-// method's own.
+// method's own, with the couplings that deflation drops put back wherever they
+// count at first order (rows: bwd_defl_sums; rho: k_bwd_merge).
 #pragma once
 #include "tde_device.h"
 
@@ -563,13 +564,15 @@ TDE_DEV void body_bwd_leaf_out(const LeafRec& L, int r, const Grad& gr, const do
 }
 
 // Tear coupling of merge m: beta = e[c] (scaled), rho~ = 2|beta| and the torn
-// diagonal entries d'_c = d_c - |beta|, d'_{c+1} = d_{c+1} - |beta|.  At beta = 0
-// the problem decouples and the derivative is 0.
+// diagonal entries d'_c = d_c - |beta|, d'_{c+1} = d_{c+1} - |beta|.  At beta = 0,
+// and where every column deflates, the problem decouples: the eigenvalues
+// depend on beta^2 alone, and the derivative is 0 (to tol over the gaps).
+constexpr double kDecoupled = INFINITY;
 TDE_DEV void body_bwd_tear(const MergeRec& R, double grho, const double* __restrict__ e,
                            const unsigned long long* __restrict__ pmax, const Grad& gr, double* ge) {
     const long long c = R.off + R.nL - 1;
     const double beta = e[c];
-    if (beta == 0.0) {
+    if (beta == 0.0 || grho == kDecoupled) {
         ge[c] = 0.0;
         return;
     }

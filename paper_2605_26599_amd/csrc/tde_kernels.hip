@@ -2943,24 +2943,78 @@ __device__ __forceinline__ void bwd_negl_block(int b, const MergeRec* __restrict
     if (sub == 0) gr.gZ[t] = gz;
 }
 
-// dL/drho~ of merge m: sum_k gtot_k / (rho^2 N_k^2), one workgroup.
+// dL/drho~ of merge m, one workgroup: sum_k gtot_k / (rho^2 N_k^2) over the
+// secular roots, and what deflation takes out of the secular equation.  A
+// negligible column p still moves by rho z_p^2 and is coupled to the secular
+// columns by rho z_p z_i and to the other negligible ones by rho z_p z_q:
+// z_p (z_p dL/dD_p + dL/dz_p / rho) per column and z_p z_q X_pq / (D_p - D_q) per
+// pair (X_pq as for the dropped couplings; equal poles: nothing).  As
+// |rho z_p| <= tol these stay below 4e-12 of the adjoints over the gaps from
+// kGrhoCols and kGrhoPairs on and are left out there.  They count because the
+// tear's derivative is a difference that cancels for small couplings (random
+// matrices of 400 columns, an eighth of the couplings 1e-12, 1e-13, 1e-15 of the
+// rest: dL/de wrong by 5e-6, 1e-3, 1.9 of |w| without them, 3e-13, 3e-14, 5e-13
+// with them).  With every column deflated the children do not interact:
+// kDecoupled.
+constexpr double kGrhoCols = 1e-3, kGrhoPairs = 1e-9;  // scaled rho
 __device__ __forceinline__ void bwd_grho_block(int m, const MergeRec* __restrict__ mr, const double* __restrict__ e,
                                                const unsigned long long* __restrict__ pmax, const Work& w,
                                                const Grad& gr, long long cstride, int mstart, double* part) {
     const MergeRec R = mr[m];
     const MergeSpan sp = merge_span(R, w.scan);
     const double* mu = gr.coef + 3 * cstride + sp.ks;
+    __shared__ int wsum[16], tot;
+    double sgn;
+    const double rho = merge_rho(R, e, pmax, &sgn);
     double acc = 0.0;
     for (int k = threadIdx.x; k < sp.K; k += kWG) acc += mu[k];
+    acc /= rho * rho;
+    if (sp.K && rho < kGrhoCols) {  // block-uniform
+        const int s = R.nL + R.nR;
+        const int nr = w.scanR[R.pk + s] - w.scanR[R.pk];
+        const int nn = s - sp.K - nr;
+        const int* dp = w.dpos + (R.pk - sp.ks - w.scanR[R.pk]);
+        for (int p = threadIdx.x; p < nn; p += kWG) {
+            const long long t = dp[p];
+            const double z = w.Z[t];
+            acc += z * (z * gr.gD[t] + gr.gZ[t] / rho);
+        }
+        if (rho < kGrhoPairs && !(R.flags & MF_ROOT)) {  // block-uniform
+            // the columns that weigh anything (a few hundred where eigenvectors
+            // are localised), in order, in the runs' scratch
+            int* list = gr.sidx + R.pk;
+            int np = 0;
+            for (int p0 = 0; p0 < nn; p0 += kWG) {
+                const int p = p0 + (int)threadIdx.x;
+                const int f = (p < nn && fabs(w.Z[dp[p]]) > 1e-12) ? 1 : 0;
+                const int incl = block_incl_scan(f, wsum);
+                if (f) list[np + incl - 1] = dp[p];
+                if (threadIdx.x == kWG - 1) tot = incl;
+                __syncthreads();
+                np += tot;
+                __syncthreads();
+            }
+            for (int p = threadIdx.x; p < np; p += kWG) {
+                const long long t = list[p];
+                const double D = w.D[t], rl = w.RL[t], rh = w.RH[t], gl = gr.gRL[t], gh = gr.gRH[t];
+                double x = 0.0;
+                for (int q = 0; q < p; ++q) {
+                    const long long u = list[q];
+                    const double gap = D - w.D[u];
+                    const double X = gl * w.RL[u] + gh * w.RH[u] - gr.gRL[u] * rl - gr.gRH[u] * rh;
+                    x += (gap != 0.0) ? w.Z[u] * X / gap : 0.0;
+                }
+                acc += w.Z[t] * x;
+            }
+        }
+    }
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
         for (int i = 0; i < kWG / 64; ++i) s += part[i];
-        double sgn;
-        const double rho = merge_rho(R, e, pmax, &sgn);
-        gr.grho[mstart + m] = sp.K ? s / (rho * rho) : 0.0;
+        gr.grho[mstart + m] = sp.K ? s : kDecoupled;
     }
 }
 
@@ -2989,29 +3043,32 @@ __device__ __forceinline__ void bwd_runs_block(int b, int nb, const MergeRec* __
 }
 
 // The steps of a level after the pole adjoints, in one launch: workgroups
-// [0, nbr) the close-pole runs, [nbr, nbr + nbn) the negligible columns,
-// [nbr + nbn, nbr + nbn + M) one merge's dL/drho~ each.  All three read the
-// root coefficients and the node's adjoints and write disjoint outputs
-// (candidate columns and the runs' scratch, negligible columns, per-merge
-// rho), so they need no order among themselves, and the short ones run in
-// the long ones' shadow instead of after them.
+// [0, nbr) the close-pole runs, [nbr, nbr + nbn) the negligible columns.  Both
+// read the root coefficients and the node's adjoints and write disjoint outputs
+// (candidate columns and the runs' scratch, negligible columns), so they need no
+// order among themselves, and the short ones run in the long ones' shadow
+// instead of after them.
 template <int G>
 __global__ __launch_bounds__(kWG) void k_bwd_defl(const MergeRec* __restrict__ mr, const int* __restrict__ blkm,
-                                                  long long N, const double* __restrict__ e,
-                                                  const unsigned long long* __restrict__ pmax, Work w, Grad gr,
-                                                  long long cstride, int mstart, int nbr, int nbn) {
+                                                  long long N, Work w, Grad gr, long long cstride, int nbr) {
     if (input_nonfinite(w)) return;
-    __shared__ double part[kWG / 64];
     const int b = (int)blockIdx.x;
     if (b < nbr) bwd_runs_block<G>(b, nbr, mr, blkm, N, w, gr, cstride);
-    else if (b < nbr + nbn) bwd_negl_block<G>(b - nbr, mr, blkm, N, w, gr, cstride);
-    else bwd_grho_block(b - nbr - nbn, mr, e, pmax, w, gr, cstride, mstart, part);  // block-uniform
+    else bwd_negl_block<G>(b - nbr, mr, blkm, N, w, gr, cstride);
 }
 
+// The merged columns back to the children in workgroups [0, nb), then one
+// merge's dL/drho~ each: both read the finished adjoints of the columns.
 __global__ __launch_bounds__(kWG) void k_bwd_merge(const MergeRec* __restrict__ mr, const int* __restrict__ blkm,
                                                    long long N, const double* __restrict__ e,
-                                                   const unsigned long long* __restrict__ pmax, Work w, Grad gr) {
+                                                   const unsigned long long* __restrict__ pmax, Work w, Grad gr,
+                                                   long long cstride, int mstart, int nb) {
     if (input_nonfinite(w)) return;
+    __shared__ double part[kWG / 64];
+    if ((int)blockIdx.x >= nb) {
+        bwd_grho_block((int)blockIdx.x - nb, mr, e, pmax, w, gr, cstride, mstart, part);
+        return;
+    }
     const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (t < N) body_bwd_merge(t, merge_of(mr, blkm, t), mr, e, pmax, w, gr);
 }
@@ -3542,12 +3599,11 @@ static void launch_bwd_roots_g(int smax, int wmin, long long N, const MergeRec* 
 // The couplings deflation drops (negligible columns, rotated runs, G lanes
 // per column or run) and the merges' dL/drho~, one launch.
 template <int G>
-static void launch_bwd_defl(long long N, int M, const MergeRec* mr, const int* blkm, const double* e,
-                            const Work& w, const Grad& gr, long long cs, int mstart, void* stream) {
+static void launch_bwd_defl(long long N, const MergeRec* mr, const int* blkm, const Work& w, const Grad& gr,
+                            long long cs, void* stream) {
     const unsigned nbr = nblk(N, kWG) < 4096u ? nblk(N, kWG) : 4096u;
     const unsigned nbn = nblk(N * G, kWG);
-    TDE_LAUNCH_K(KIND_BACKWARD, k_bwd_defl<G>, nbr + nbn + (unsigned)M, kWG, stream, mr, blkm, N, e,
-                 (const unsigned long long*)w.pmax, w, gr, cs, mstart, (int)nbr, (int)nbn);
+    TDE_LAUNCH_K(KIND_BACKWARD, k_bwd_defl<G>, nbr + nbn, kWG, stream, mr, blkm, N, w, gr, cs, (int)nbr);
 }
 
 int enqueue_backward(const Plan& p, const Work& w, const Grad& gr, const Ckpt& ck, const double* d,
@@ -3588,14 +3644,14 @@ int enqueue_backward(const Plan& p, const Work& w, const Grad& gr, const Ckpt& c
             default: launch_bwd_roots_g<16>(L.smax, p.wide_min, N, mr, blkm, M, e, wl, gr, cs, stream); break;
         }
         switch (lanes_per_root(L.smax, p.sweep_cols)) {
-            case 1: launch_bwd_defl<1>(N, M, mr, blkm, e, wl, gr, cs, L.mstart, stream); break;
-            case 2: launch_bwd_defl<2>(N, M, mr, blkm, e, wl, gr, cs, L.mstart, stream); break;
-            case 4: launch_bwd_defl<4>(N, M, mr, blkm, e, wl, gr, cs, L.mstart, stream); break;
-            case 8: launch_bwd_defl<8>(N, M, mr, blkm, e, wl, gr, cs, L.mstart, stream); break;
-            default: launch_bwd_defl<16>(N, M, mr, blkm, e, wl, gr, cs, L.mstart, stream); break;
+            case 1: launch_bwd_defl<1>(N, mr, blkm, wl, gr, cs, stream); break;
+            case 2: launch_bwd_defl<2>(N, mr, blkm, wl, gr, cs, stream); break;
+            case 4: launch_bwd_defl<4>(N, mr, blkm, wl, gr, cs, stream); break;
+            case 8: launch_bwd_defl<8>(N, mr, blkm, wl, gr, cs, stream); break;
+            default: launch_bwd_defl<16>(N, mr, blkm, wl, gr, cs, stream); break;
         }
-        TDE_LAUNCH_K(KIND_BACKWARD, k_bwd_merge, nb, kWG, stream, mr, blkm, N, e, (const unsigned long long*)w.pmax,
-                     wl, gr);
+        TDE_LAUNCH_K(KIND_BACKWARD, k_bwd_merge, nb + (unsigned)M, kWG, stream, mr, blkm, N, e,
+                     (const unsigned long long*)w.pmax, wl, gr, cs, L.mstart, (int)nb);
     }
     if (p.nleaves > 0) {
         if (p.leafmax <= 8)

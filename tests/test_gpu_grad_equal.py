@@ -33,7 +33,8 @@ def _t(x):
 
 @pytest.mark.parametrize("n,leaf", [(4, 1), (5, 1), (5, 2), (6, 2)])
 def test_integer_matrices(tde, n, leaf):
-    probs = [(d, e) for d in itertools.product([0.0, 1.0], repeat=n) for e in itertools.product([0.0, 1.0], repeat=n - 1)]
+    probs = [(d, e) for d in itertools.product([0.0, 1.0], repeat=n)
+             for e in itertools.product([0.0, 1.0], repeat=n - 1)]
     print(f"[gpu-grad-equal] n={n} leaf={leaf} problems={len(probs)}", flush=True)
     d = np.array([p[0] for p in probs])
     e = np.array([p[1] + (0.0,) for p in probs])
