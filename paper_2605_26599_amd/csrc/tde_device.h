@@ -70,13 +70,15 @@ TDE_DEV double bitsd(unsigned long long u) {
 }
 
 // Exact power-of-two scale 2^ceil(log2 max|T_ij|) of a problem (driver-level
-// scaling of unreduced blocks, Section 4.2); 1 for the zero matrix.
+// scaling of unreduced blocks, Section 4.2); 1 for the zero matrix.  Kept where
+// the power and its reciprocal are both finite: entries from 2^1023 on scale to
+// [1, 2), all of them below 2^-1024 to less than 1/2.
 TDE_DEV double scale_of(unsigned long long maxbits) {
     double mx = bitsd(maxbits);
     if (!(mx > 0.0) || !(mx <= DBL_MAX)) return 1.0;
     int ex;
     frexp(mx, &ex);
-    return ldexp(1.0, ex);
+    return ldexp(1.0, ex > 1023 ? 1023 : (ex < -1023 ? -1023 : ex));
 }
 
 // Largest m in [lo, hi] with mr[m].pk <= t (merge lookup within a range known

@@ -81,3 +81,18 @@ def test_gradients_of_small_scaled_problems(tde):
         res.append([x.cpu().numpy() for x in (lam / s, gd, ge)])
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("leaf", [1, 32])
+def test_ends_of_the_range(tde, leaf):
+    """Largest entries above 2^1023, and matrices of denormals: 64 of the
+    smallest denormals of absolute error, or of eps of the norm."""
+    n = 40
+    d, e = tdgen.tridiag("wilkinson", n)
+    ref = oracle.eigvals(d, e)
+    big = 1.9 * 2.0 ** 1023 / np.abs(ref).max()
+    for s, unit in ((2.0 ** -1072, 2.0 ** -1074), (2.0 ** -1030, 2.0 ** -1074), (big, 2.0 ** -52 * 1.9 * 2.0 ** 1023)):
+        print(f"[gpu-scale] ends of the range scale={s:g} leaf={leaf}", flush=True)
+        lam = tde.eigvals(_t(d * s), _t(e * s), leaf=leaf).cpu().numpy()
+        assert np.isfinite(lam).all() and np.all(np.diff(lam) >= 0.0)
+        assert np.abs(lam - ref * s).max() <= 64.0 * unit
